@@ -113,18 +113,85 @@ __global__ __launch_bounds__(kBlock) void k_moments_final(
   }
 }
 
-// rho[site] = dvd * sum_j f[j][site], FP64, j in order.
+// rho[site] = dvd * sum_j f[j][site] in FP64.  Bound by the one read of the
+// state; a lane per site walking all the planes leaves too few loads in
+// flight when the sites are few and the planes many.  Here NW wavefronts
+// share 64 VEC consecutive sites: wavefront w adds planes w, w + NW, ...
+// (eight loads in flight), and the NW sums are added in wavefront order.
+// The order of the additions depends only on the sizes.  Measured against a
+// lane per site: 128^2 x 65^2 1422 -> 41 us (6.7 TB/s), 512^2 x 33^2 492 ->
+// 212 us (5.4 TB/s), 192^2 x 17^2 FP64 70 -> 14 us.
+template <typename T, int VEC>
+struct alignas(sizeof(T) * VEC) SiteVec {
+  T v[VEC];
+};
+
+template <typename T, int VEC, int NW>
+__global__ __launch_bounds__(64 * NW) void k_density(
+    const T* __restrict__ f, int64_t sites, int64_t pitch, int nplanes,
+    double dvd, double* __restrict__ rho) {
+  using V = SiteVec<T, VEC>;
+  __shared__ double sh[NW][64 * VEC];
+  const int l = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
+  const int64_t s0 = (int64_t)blockIdx.x * (64 * VEC);
+  const int64_t i = s0 + l * VEC;
+  double a[VEC] = {};
+  if (i < sites) {  // VEC divides sites
+    const T* p = f + i;
+    int j = w;
+    for (; j + 7 * NW < nplanes; j += 8 * NW) {
+      V v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        v[k] = *(const V*)(p + (size_t)(j + k * NW) * pitch);
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) a[e] += (double)v[k].v[e];
+    }
+    for (; j < nplanes; j += NW) {
+      const V v = *(const V*)(p + (size_t)j * pitch);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) a[e] += (double)v.v[e];
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) sh[w][l * VEC + e] = a[e];
+  __syncthreads();
+  for (int t = (int)threadIdx.x; t < 64 * VEC; t += 64 * NW) {
+    if (s0 + t >= sites) break;
+    double r = sh[0][t];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) r += sh[q][t];
+    rho[s0 + t] = dvd * r;
+  }
+}
+
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_density(const T* __restrict__ f,
-                                                    int64_t sites,
-                                                    int64_t pitch, int nplanes,
-                                                    double dvd,
-                                                    double* __restrict__ rho) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= sites) return;
-  double acc = 0.0;
-  for (int j = 0; j < nplanes; ++j) acc += (double)f[(size_t)j * pitch + i];
-  rho[i] = dvd * acc;
+void density_go(const T* f, int64_t sites, int64_t pitch, int nplanes,
+                double dvd, double* rho, hipStream_t s) {
+  // 16-byte loads once they still leave two workgroups per compute unit,
+  // and only where every plane and the sites allow the alignment
+  constexpr int VEC = 16 / (int)sizeof(T);
+  const bool wide = sites >= (int64_t)64 * VEC * 512 && sites % VEC == 0 &&
+                    pitch % VEC == 0 && ((uintptr_t)f & 15) == 0;
+  auto go = [&](auto kernel, int vec, int nw) {
+    const int64_t g = (sites + 64 * vec - 1) / (64 * vec);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(64 * nw), 0, s, f,
+                       sites, pitch, nplanes, dvd, rho);
+  };
+  // 16 wavefronts where each still has a run of planes to add
+  if (nplanes >= 64) {
+    if (wide)
+      go(k_density<T, VEC, 16>, VEC, 16);
+    else
+      go(k_density<T, 1, 16>, 1, 16);
+  } else {
+    if (wide)
+      go(k_density<T, VEC, 4>, VEC, 4);
+    else
+      go(k_density<T, 1, 4>, 1, 4);
+  }
 }
 
 // Flow check: flag |= 1 if some |u| exceeds umax_ok (>= when strict) or is
@@ -222,13 +289,10 @@ hipError_t launch_moments(const void* f, int64_t sites, int64_t pitch,
 hipError_t launch_density(const void* f, int64_t sites, int64_t pitch,
                           int nplanes, int f64, double dvd, double* rho,
                           hipStream_t s) {
-  const int g = (int)((sites + kBlock - 1) / kBlock);
   if (f64)
-    hipLaunchKernelGGL(k_density<double>, dim3(g), dim3(kBlock), 0, s,
-                       (const double*)f, sites, pitch, nplanes, dvd, rho);
+    density_go((const double*)f, sites, pitch, nplanes, dvd, rho, s);
   else
-    hipLaunchKernelGGL(k_density<float>, dim3(g), dim3(kBlock), 0, s,
-                       (const float*)f, sites, pitch, nplanes, dvd, rho);
+    density_go((const float*)f, sites, pitch, nplanes, dvd, rho, s);
   return hipGetLastError();
 }
 
