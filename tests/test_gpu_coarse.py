@@ -51,6 +51,28 @@ def test_restrict_matches_oracle(dim, nvf):
     assert rel_l2(got, want) < 1e-6
 
 
+@pytest.mark.parametrize("nvf,sites", [(5, 1), (9, 255), (13, 257),
+                                       (65, 6656), (33, 20737),
+                                       (9, 131072), (5, 524289)])
+def test_restrict_blocks_of_coarse_cells(nvf, sites):
+    """Both block shapes (2 x 2 coarse cells per thread from 2048
+    workgroups on), odd and even coarse counts, ragged site counts.  A
+    coarse value adds 25 non-negative terms with exact weights: 25 roundings
+    of 2^-24."""
+    import torch
+    from oracle import coarse as C
+    from paper_1508_02899_amd import restrict
+    g = torch.Generator(device="cuda")
+    g.manual_seed(nvf + sites)
+    f = torch.rand((nvf * nvf, sites), generator=g, device="cuda")
+    R = torch.from_numpy(C.restrict_weights(nvf)).cuda() / 4.0
+    c = f.double().view(nvf, nvf, sites)
+    want = torch.tensordot(R, torch.tensordot(R, c, ([1], [0])),
+                           ([1], [1])).transpose(0, 1)
+    got = restrict(f, 2).double().view_as(want)
+    assert float(((got - want) / want).abs().max()) <= 25 * 2.0 ** -24
+
+
 def test_mlp_forward_matrix_cores_match_oracle():
     """bf16 weights and layer inputs, FP32 accumulation on the matrix cores
     vs the FP64 oracle with the same bf16 roundings."""
