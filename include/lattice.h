@@ -239,8 +239,8 @@ int lattice_density(lattice_t* L, const void* f, double dt, double* rho);
  * m_b the density summed over box b, N_b the number of boxes (so that
  * <rho_r> = 1).  out: host, levels doubles.  nx (and ny in 2D) must be
  * multiples of 2^(levels-1); levels <= 32.  FP64 sums in a fixed order
- * (bit-reproducible).  Synchronous; allocates a temporary device
- * workspace.  EINVAL, ENOMEM, ENONFINITE (zero or non-finite mass), EHIP.
+ * (bit-reproducible).  Synchronous; the first call allocates a small device
+ * workspace that the handle keeps.  EINVAL, ENOMEM, ENONFINITE (zero or non-finite mass), EHIP.
  */
 int lattice_rho_r2(lattice_t* L, const double* rho, int levels, double* out);
 

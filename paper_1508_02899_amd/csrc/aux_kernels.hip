@@ -78,30 +78,47 @@ __global__ __launch_bounds__(kBlock) void k_plane_sums(const T* __restrict__ f,
 
 // Weighted combination of the plane sums: M = w sum S_j, P_k = w sum S_j v_k,
 // Q_k = w sum S_j v_k^2 with v = (j - h) dv per component, and the variance
-// sum_k Q_k/M - |P/M|^2.  Single workgroup, fixed order.
-__global__ __launch_bounds__(kBlock) void k_moments_final(
+// sum_k Q_k/M - |P/M|^2.  Single workgroup, fixed order: lanes and then
+// wavefronts by a tree.  Latency-bound: the five sums go through one tree
+// together (4225 planes: 5.5 us; 9.3 us with 256 threads and a tree per sum).
+constexpr int kMomWaves = 16;
+__global__ __launch_bounds__(64 * kMomWaves) void k_moments_final(
     const double* __restrict__ ps, int nv, int dim, double w, double dv,
     const int* __restrict__ flag, double* __restrict__ out) {
-  __shared__ double sh[kBlock];
+  __shared__ double sh[kMomWaves][5];
   const int h = (nv - 1) / 2;
   const int nplanes = dim == 1 ? nv : nv * nv;
-  double m = 0, px = 0, py = 0, qx = 0, qy = 0;
-  for (int j = threadIdx.x; j < nplanes; j += kBlock) {
+  double a[5] = {};  // m, px, py, qx, qy
+#pragma unroll 4
+  for (int j = threadIdx.x; j < nplanes; j += 64 * kMomWaves) {
     const double s = ps[j];
-    const double vx = (double)((dim == 1 ? j : j % nv) - h) * dv;
-    const double vy = dim == 2 ? (double)(j / nv - h) * dv : 0.0;
-    m += s;
-    px += s * vx;
-    qx += s * vx * vx;
-    py += s * vy;
-    qy += s * vy * vy;
+    const int jy = dim == 2 ? j / nv : 0;
+    const double vx = (double)(j - jy * nv - h) * dv;
+    const double vy = dim == 2 ? (double)(jy - h) * dv : 0.0;
+    a[0] += s;
+    a[1] += s * vx;
+    a[3] += s * vx * vx;
+    a[2] += s * vy;
+    a[4] += s * vy * vy;
   }
-  m = block_sum(m, sh);
-  px = block_sum(px, sh);
-  py = block_sum(py, sh);
-  qx = block_sum(qx, sh);
-  qy = block_sum(qy, sh);
-  if (threadIdx.x == 0) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int k = 0; k < 5; ++k) a[k] += __shfl_xor(a[k], o);
+  const int l = (int)threadIdx.x & 63, q = (int)threadIdx.x >> 6;
+  if (l == 0)
+#pragma unroll
+    for (int k = 0; k < 5; ++k) sh[q][k] = a[k];
+  __syncthreads();
+  if (q != 0) return;
+#pragma unroll
+  for (int k = 0; k < 5; ++k) a[k] = sh[l % kMomWaves][k];
+#pragma unroll
+  for (int o = kMomWaves / 2; o > 0; o >>= 1)
+#pragma unroll
+    for (int k = 0; k < 5; ++k) a[k] += __shfl_xor(a[k], o);
+  if (l == 0) {
+    const double m = a[0], px = a[1], py = a[2], qx = a[3], qy = a[4];
     out[0] = w * m;
     out[1] = w * px;
     out[2] = w * py;
@@ -281,8 +298,8 @@ hipError_t launch_moments(const void* f, int64_t sites, int64_t pitch,
   else
     hipLaunchKernelGGL(k_plane_sums<float>, dim3(nplanes), dim3(kBlock), 0, s,
                        (const float*)f, sites, pitch, plane_sums);
-  hipLaunchKernelGGL(k_moments_final, dim3(1), dim3(kBlock), 0, s, plane_sums,
-                     nv, dim, w, dv, flag, out);
+  hipLaunchKernelGGL(k_moments_final, dim3(1), dim3(64 * kMomWaves), 0, s,
+                     plane_sums, nv, dim, w, dv, flag, out);
   return hipGetLastError();
 }
 

@@ -186,7 +186,7 @@ int lattice_init(const lattice_desc* d, lattice_t** out) {
       hipMalloc(&L->plane_sums, sizeof(double) * (size_t)L->nplanes) !=
           hipSuccess ||
       hipMalloc(&L->red, sizeof(double) * 8) != hipSuccess ||
-      hipHostMalloc((void**)&L->host_red, sizeof(double) * 8,
+      hipHostMalloc((void**)&L->host_red, sizeof(double) * lat::kRhoMaxLevels,
                     hipHostMallocDefault) != hipSuccess) {
     lattice_destroy(L);
     return LATTICE_ENOMEM;
@@ -523,24 +523,24 @@ int lattice_rho_r2(lattice_t* L, const double* rho, int levels, double* out) {
   if (d.nx % tile != 0 || (d.dim == 2 && d.ny % tile != 0))
     return set_err(L, LATTICE_EINVAL,
                    "nx (and ny) must be multiples of 2^(levels-1)");
-  const int64_t npart = lat::rho_r2_partials(d.dim, d.nx, d.ny, levels);
-  double* work = nullptr;
-  if (hipMalloc(&work, sizeof(double) * (size_t)(L->sites + 2 * npart +
-                                                 levels)) != hipSuccess)
-    return set_err(L, LATTICE_ENOMEM, "rho_r2 workspace");
-  double* partial = work + L->sites;
-  double* dout = partial + 2 * npart;
-  hipError_t e = lat::launch_rho_r2(rho, d.dim, d.nx, d.ny, levels, work,
-                                    partial, dout, L->stream);
+  if (!L->obs_work) {
+    const int64_t n = lat::rho_r2_work(d.dim, d.nx, d.ny);
+    if (hipMalloc(&L->obs_work, sizeof(double) * (size_t)n) != hipSuccess) {
+      L->obs_work = nullptr;
+      return set_err(L, LATTICE_ENOMEM, "rho_r2 workspace");
+    }
+  }
+  hipError_t e = lat::launch_rho_r2(rho, d.dim, d.nx, d.ny, levels,
+                                    L->obs_work, L->stream);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(out, dout, sizeof(double) * levels,
+    e = hipMemcpyAsync(L->host_red, L->obs_work, sizeof(double) * levels,
                        hipMemcpyDeviceToHost, L->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-  (void)hipFree(work);
   if (e != hipSuccess) {
     (void)hipGetLastError();
-    return set_err(L, LATTICE_EHIP, hipGetErrorString(e));
+    return set_err(L, LATTICE_EHIP, "%s", hipGetErrorString(e));
   }
+  memcpy(out, L->host_red, sizeof(double) * levels);
   for (int k = 0; k < levels; ++k)
     if (!isfinite(out[k]))
       return set_err(L, LATTICE_ENONFINITE, "rho_r2 not finite");
@@ -627,6 +627,7 @@ int lattice_destroy(lattice_t* L) {
   if (L->flag) (void)hipFree(L->flag);
   if (L->plane_sums) (void)hipFree(L->plane_sums);
   if (L->red) (void)hipFree(L->red);
+  if (L->obs_work) (void)hipFree(L->obs_work);
   if (L->host_red) (void)hipHostFree(L->host_red);
   for (hipEvent_t e : L->ev) (void)hipEventDestroy(e);
   delete L;

@@ -63,10 +63,11 @@ hipError_t launch_moments(const void* f, int64_t sites, int64_t pitch,
 // rho[site] = dvd * sum_j f[j][site] in FP64.
 // <rho_r^2> on tilings r = 2^k sites, k = 0..levels-1 (observables.hip).
 constexpr int kRhoMaxLevels = 32;
-int64_t rho_r2_partials(int dim, int64_t nx, int64_t ny, int levels);
+// work: rho_r2_work doubles, enough for any number of levels; the results
+// are its first `levels` values.
+int64_t rho_r2_work(int dim, int64_t nx, int64_t ny);
 hipError_t launch_rho_r2(const double* rho, int dim, int64_t nx, int64_t ny,
-                         int levels, double* work, double* partial,
-                         double* out, hipStream_t s);
+                         int levels, double* work, hipStream_t s);
 hipError_t launch_density(const void* f, int64_t sites, int64_t pitch,
                           int nplanes, int f64, double dvd, double* rho,
                           hipStream_t s);

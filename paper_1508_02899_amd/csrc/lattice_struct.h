@@ -21,7 +21,8 @@ struct lattice {
   int* flag = nullptr;          // sticky CFL / finiteness flag (device)
   double* plane_sums = nullptr; // nplanes doubles
   double* red = nullptr;        // 8 doubles: moments / absmax
-  double* host_red = nullptr;   // pinned mirror of red
+  double* host_red = nullptr;   // pinned: mirror of red, <rho_r^2> values
+  double* obs_work = nullptr;   // lattice_rho_r2, from its first call on
   char msg[512];
   // profiling
   bool prof = false;

@@ -5,8 +5,14 @@
 // rather than sliding): the box mass m_b is the sum of the site densities
 // inside, rho_r = (m_b / M) * N_b so that <rho_r> = 1, and
 //   <rho_r^2> = N_b * sum_b m_b^2 / M^2.
-// Level k + 1 box masses are the sums of 2^dim level-k boxes, so each level
-// reads the previous one.  All sums are FP64 in a fixed order.
+// Level k + 1 box masses are the sums of 2^dim level-k boxes.  All sums are
+// FP64 in a fixed order.
+//
+// Bound by launches and latency, not by bytes (a density is 0.1 to 2 MB): a
+// workgroup takes a tile of 32 x 32 sites (1024 in 1D) through all the levels
+// inside it (6; 11 in 1D), a second stage does the same on the tiles' masses,
+// and a last stage of one workgroup also combines the levels.  8 levels at
+// 128^2: 2 launches, 11 us; a launch per level: 9 launches, 39 us.
 #include "device_common.h"
 #include "lattice_internal.h"
 
@@ -15,123 +21,202 @@ namespace {
 
 constexpr int kObsBlock = 256;
 constexpr int kMaxLevels = kRhoMaxLevels;
+constexpr int kTile = 1024;  // sites per workgroup: 32 x 32, or 1024 in 1D
 
-__device__ void block_sum2(double& a, double& b, double* sa, double* sb) {
-  const int t = (int)threadIdx.x;
-  sa[t] = a;
-  sb[t] = b;
-  __syncthreads();
-#pragma unroll
-  for (int w = kObsBlock / 2; w > 0; w >>= 1) {
-    if (t < w) {
-      sa[t] = sa[t] + sa[t + w];
-      sb[t] = sb[t] + sb[t + w];
-    }
-    __syncthreads();
-  }
-  a = sa[0];
-  b = sb[0];
-  __syncthreads();
-}
-
-// One thread per output box.  mode 0: boxes are the input cells themselves
-// (level 0); mode 1: 2 x 2 children (2D), mode 2: 2 children (1D).
-// partial[2 * block] = sum m, partial[2 * block + 1] = sum m^2.
-__global__ __launch_bounds__(kObsBlock) void k_tile_level(
-    const double* __restrict__ m_in, int64_t nx_out, int64_t ny_out,
-    int mode, double* __restrict__ m_out, double* __restrict__ partial) {
-  __shared__ double sa[kObsBlock], sb[kObsBlock];
-  const int64_t n = nx_out * ny_out;
-  const int64_t i = (int64_t)blockIdx.x * kObsBlock + threadIdx.x;
-  double m = 0.0;
-  if (i < n) {
-    if (mode == 0) {
-      m = m_in[i];
-    } else if (mode == 2) {
-      m = m_in[2 * i] + m_in[2 * i + 1];
-    } else {
-      const int64_t y = i / nx_out, x = i - y * nx_out;
-      const int64_t nx_in = 2 * nx_out;
-      const double* r0 = m_in + (2 * y) * nx_in + 2 * x;
-      const double* r1 = r0 + nx_in;
-      m = (r0[0] + r0[1]) + (r1[0] + r1[1]);
-    }
-    if (m_out) m_out[i] = m;
-  }
-  double s1 = m, s2 = m * m;
-  block_sum2(s1, s2, sa, sb);
-  if (threadIdx.x == 0) {
-    partial[2 * blockIdx.x] = s1;
-    partial[2 * blockIdx.x + 1] = s2;
-  }
-}
+// Levels that one tile holds: boxes of 1 .. 32 (1 .. 1024) sites per side.
+constexpr int stage_levels(int dim) { return dim == 2 ? 6 : 11; }
 
 struct LevelMeta {
   int64_t off[kMaxLevels], nblk[kMaxLevels], nbox[kMaxLevels];
 };
 
-// One block per level: fixed-order sum of that level's partials, then
-// out[k] = N_b * sum m^2 / (sum m)^2.
-__global__ __launch_bounds__(kObsBlock) void k_tile_final(
-    const double* __restrict__ partial, LevelMeta meta,
-    double* __restrict__ out) {
-  __shared__ double sa[kObsBlock], sb[kObsBlock];
-  const int k = blockIdx.x;
-  const double* p = partial + 2 * meta.off[k];
-  double s1 = 0.0, s2 = 0.0;
-  for (int64_t j = threadIdx.x; j < meta.nblk[k]; j += kObsBlock) {
-    s1 += p[2 * j];
-    s2 += p[2 * j + 1];
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+// out[k] = N_b * sum m^2 / (sum m)^2 from level k's partial sums; levels
+// q, q + 4, ... by wavefront q.
+__device__ void combine_levels(const double* partial, const LevelMeta& meta,
+                               int levels, double* out) {
+  const int l = (int)threadIdx.x & 63;
+  for (int k = (int)threadIdx.x >> 6; k < levels; k += kObsBlock / 64) {
+    const double* p = partial + 2 * meta.off[k];
+    double s1 = 0.0, s2 = 0.0;
+    for (int64_t j = l; j < meta.nblk[k]; j += 64) {
+      s1 += p[2 * j];
+      s2 += p[2 * j + 1];
+    }
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if (l == 0) out[k] = (double)meta.nbox[k] * s2 / (s1 * s1);
   }
-  block_sum2(s1, s2, sa, sb);
-  if (threadIdx.x == 0) out[k] = (double)meta.nbox[k] * s2 / (s1 * s1);
+}
+
+// One stage: the box masses m_in[ny][nx] of level `base` (the sites when
+// base = 0) are summed over the boxes of levels base .. base + nlev - 1.
+// Sums of m and m^2 of level k over this tile go to partial[2 (off[k] +
+// tile)]; level `base` itself only in the first stage (the stage before has
+// done it).  Boxes lie wholly inside or outside the array (nx and ny are
+// multiples of the largest box), so cells outside count as zeros.  m_out
+// (when not NULL) gets the mass of the whole tile.
+template <int DIM>
+__global__ __launch_bounds__(kObsBlock) void k_tile_stage(
+    const double* __restrict__ m_in, int64_t nx, int64_t ny, int64_t ntx,
+    int base, int nlev, LevelMeta meta, double* partial,
+    double* __restrict__ m_out, int levels, double* __restrict__ out) {
+  constexpr int NL = stage_levels(DIM);
+  __shared__ double box[kObsBlock], red[NL][kObsBlock / 64][2];
+  const int t = (int)threadIdx.x, l = t & 63, w = t >> 6;
+  const int64_t tile = blockIdx.x;
+  double v[4];  // 2 x 2 sites (2D) or 4 consecutive ones (1D)
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    int64_t x, y;
+    if (DIM == 2) {
+      const int64_t ty = tile / ntx, tx = tile - ty * ntx;
+      x = tx * 32 + 2 * (t & 15) + (e & 1);
+      y = ty * 32 + 2 * (t >> 4) + (e >> 1);
+    } else {
+      x = tile * kTile + 4 * t + e;
+      y = 0;
+    }
+    v[e] = x < nx && y < ny ? m_in[y * nx + x] : 0.0;
+  }
+  auto note = [&](int k, double s1, double s2) {
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if (l == 0) {
+      red[k][w][0] = s1;
+      red[k][w][1] = s2;
+    }
+  };
+  note(0, (v[0] + v[1]) + (v[2] + v[3]),
+       (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]));
+  const double a = v[0] + v[1], b = v[2] + v[3];
+  double m = a + b;
+  int k = 1;
+  if (DIM == 1) {
+    note(1, m, a * a + b * b);
+    k = 2;
+  }
+  note(k, m, m * m);
+  // the remaining levels halve the number of boxes (per side)
+  int side = DIM == 2 ? 16 : kObsBlock;  // boxes (per side) of level k
+  for (++k; k < nlev; ++k) {
+    __syncthreads();
+    if (t < (DIM == 2 ? side * side : side)) box[t] = m;
+    __syncthreads();
+    const int half = side / 2;
+    const bool in = t < (DIM == 2 ? half * half : half);
+    m = 0.0;
+    if (in && DIM == 2) {
+      const double* r = box + (2 * (t / half)) * side + 2 * (t % half);
+      m = (r[0] + r[1]) + (r[side] + r[side + 1]);
+    } else if (in) {
+      m = box[2 * t] + box[2 * t + 1];
+    }
+    side = half;
+    note(k, m, m * m);
+  }
+  if (t == 0 && m_out) m_out[tile] = m;
+  __syncthreads();
+  if (t < nlev && (t > 0 || base == 0)) {
+    double s1 = red[t][0][0], s2 = red[t][0][1];
+#pragma unroll
+    for (int q = 1; q < kObsBlock / 64; ++q) {
+      s1 += red[t][q][0];
+      s2 += red[t][q][1];
+    }
+    double* p = partial + 2 * (meta.off[base + t] + tile);
+    p[0] = s1;
+    p[1] = s2;
+  }
+  if (out) {  // the last stage, one workgroup
+    __threadfence_block();
+    __syncthreads();
+    combine_levels(partial, meta, levels, out);
+  }
+}
+
+__global__ __launch_bounds__(kObsBlock) void k_tile_combine(
+    const double* __restrict__ partial, LevelMeta meta, int levels,
+    double* __restrict__ out) {
+  combine_levels(partial, meta, levels, out);
+}
+
+struct Stage {
+  int64_t nx, ny, ntx, tiles;  // input boxes, tiles
+};
+
+Stage stage_of(int dim, int64_t nx, int64_t ny) {
+  const int64_t ntx = dim == 2 ? (nx + 31) / 32 : (nx + kTile - 1) / kTile;
+  return {nx, ny, ntx, dim == 2 ? ntx * ((ny + 31) / 32) : ntx};
 }
 
 }  // namespace
 
-int64_t rho_r2_partials(int dim, int64_t nx, int64_t ny, int levels) {
-  int64_t cx = nx, cy = dim == 2 ? ny : 1, total = 0;
-  for (int k = 0; k < levels; ++k) {
-    if (k > 0) {
-      cx /= 2;
-      if (dim == 2) cy /= 2;
-    }
-    total += (cx * cy + kObsBlock - 1) / kObsBlock;
+int64_t rho_r2_work(int dim, int64_t nx, int64_t ny) {
+  // every level's partials (a pair per tile of its stage), the tile masses
+  // of every stage, the results
+  int64_t n = kMaxLevels;
+  Stage st = stage_of(dim, nx, dim == 2 ? ny : 1);
+  for (int base = 0; base < kMaxLevels; base += stage_levels(dim) - 1) {
+    n += (2 * stage_levels(dim) + 1) * st.tiles;
+    st = stage_of(dim, st.ntx, st.tiles / st.ntx);
   }
-  return total;
+  return n;
 }
 
 hipError_t launch_rho_r2(const double* rho, int dim, int64_t nx, int64_t ny,
-                         int levels, double* work, double* partial,
-                         double* out, hipStream_t s) {
-  // work: every level's box masses after level 0 (fewer than the sites);
-  // partial: 2 doubles per block of every level (rho_r2_partials blocks).
-  LevelMeta meta;
+                         int levels, double* work, hipStream_t s) {
+  LevelMeta meta = {};
+  double* const out = work;
   const double* in = rho;
-  double* w = work;
-  int64_t cx = nx, cy = dim == 2 ? ny : 1, poff = 0;
-  for (int k = 0; k < levels; ++k) {
-    if (k > 0) {
-      cx /= 2;
-      if (dim == 2) cy /= 2;
+  const int NL = stage_levels(dim);
+  // sizes of the stages, then their launches
+  Stage st[kMaxLevels];
+  int nst = 0;
+  int64_t poff = 0, n = nx * (dim == 2 ? ny : 1);
+  for (int base = 0; base < levels; base += NL - 1) {
+    if (base > 0 && base == levels - 1) break;  // done by the stage before
+    const Stage* p = nst ? &st[nst - 1] : nullptr;
+    st[nst] = p ? stage_of(dim, p->ntx, p->tiles / p->ntx)
+                : stage_of(dim, nx, dim == 2 ? ny : 1);
+    for (int k = base ? base + 1 : 0; k < levels && k < base + NL; ++k) {
+      meta.off[k] = poff;
+      meta.nblk[k] = st[nst].tiles;
+      meta.nbox[k] = n >> (dim * k);
+      poff += st[nst].tiles;
     }
-    const int64_t n = cx * cy;
-    const int64_t nb = (n + kObsBlock - 1) / kObsBlock;
-    const int mode = k == 0 ? 0 : (dim == 2 ? 1 : 2);
-    double* o = k == 0 ? nullptr : w;
-    hipLaunchKernelGGL(k_tile_level, dim3((unsigned)nb), dim3(kObsBlock), 0, s,
-                       k == 0 ? rho : in, cx, cy, mode, o, partial + 2 * poff);
-    meta.off[k] = poff;
-    meta.nblk[k] = nb;
-    meta.nbox[k] = n;
-    poff += nb;
-    if (k > 0) {
-      in = o;
-      w += n;
-    }
+    ++nst;
   }
-  hipLaunchKernelGGL(k_tile_final, dim3(levels), dim3(kObsBlock), 0, s,
-                     partial, meta, out);
+  double* const partial = work + kMaxLevels;
+  double* masses = partial + 2 * poff;
+  bool combined = false;
+  for (int i = 0; i < nst; ++i) {
+    const int base = i * (NL - 1);
+    const int nlev = levels - base < NL ? levels - base : NL;
+    const bool last = i == nst - 1;
+    double* const mo = last ? nullptr : masses;
+    combined = last && st[i].tiles == 1;
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)st[i].tiles),
+                         dim3(kObsBlock), 0, s, in, st[i].nx, st[i].ny,
+                         st[i].ntx, base, nlev, meta, partial, mo, levels,
+                         combined ? out : nullptr);
+    };
+    if (dim == 2)
+      go(k_tile_stage<2>);
+    else
+      go(k_tile_stage<1>);
+    in = mo;
+    masses += st[i].tiles;
+  }
+  if (!combined)
+    hipLaunchKernelGGL(k_tile_combine, dim3(1), dim3(kObsBlock), 0, s, partial,
+                       meta, levels, out);
   return hipGetLastError();
 }
 

@@ -34,6 +34,30 @@ def test_rho_r2_matches_oracle(dim, nx, ny, levels):
     lat.close()
 
 
+@pytest.mark.parametrize("dim,nx,ny,levels", [
+    (2, 31, 33, 1), (2, 34, 2, 2), (2, 96, 160, 6), (2, 64, 192, 7),
+    (2, 128, 128, 8), (2, 2048, 1024, 11), (2, 1024, 3072, 7),
+    (1, 1023, 1, 1), (1, 3 * 1024, 1, 11), (1, 4096, 1, 12),
+    (1, 1 << 21, 1, 22), (1, 7 << 14, 1, 15)])
+def test_rho_r2_stages_match_oracle(dim, nx, ny, levels):
+    """Edge tiles, one and two stages, a last stage of one and of several
+    workgroups.  Positive sums of n terms in any order agree within n 2^-53
+    each (pairwise: far below 1e-12 here)."""
+    import torch
+    from oracle import observables as O
+    from paper_1508_02899_amd import Lattice, LatticeSpec
+    rng = np.random.default_rng(nx + ny)
+    rho = rng.random((ny, nx)) ** 4 + 1e-3
+    lat = Lattice(LatticeSpec(dim=dim, nx=nx, ny=ny, nv=3, dx=0.1))
+    rd = torch.from_numpy(rho).cuda()
+    got = lat.rho_r2(rd, levels)
+    np.testing.assert_allclose(
+        got, O.rho_r2(rho if dim == 2 else rho[0], levels), rtol=1e-12)
+    assert np.array_equal(got[:1], lat.rho_r2(rd, 1))
+    assert np.array_equal(got, lat.rho_r2(rd, levels))
+    lat.close()
+
+
 def test_rho_r2_rejects_bad_tiling():
     import torch
     from paper_1508_02899_amd import Lattice, LatticeSpec, LatticeError
