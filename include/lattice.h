@@ -268,8 +268,9 @@ int lattice_rho_r2_error(const double* a, const double* b, int levels,
  * velocity square; the estimate is the mean of the separations r e_x and
  * r e_y.  out: host, nr doubles.  FP64 correlation sums in a fixed order;
  * in 2D the velocity-space product runs as one GEMM (rocBLAS) in the state
- * dtype.  Synchronous; allocates a temporary device workspace of one state
- * plus (2D) an nv^2 x nv^2 matrix.  EINVAL, ENOMEM, ENONFINITE, EHIP.
+ * dtype.  Synchronous; uses the handle's scratch buffer, and the first call
+ * allocates a workspace and (2D) an nv^2 x nv^2 matrix and a rocBLAS handle
+ * that the handle keeps.  EINVAL, ENOMEM, ENONFINITE, EHIP.
  */
 int lattice_s1(lattice_t* L, const void* f, double dt, int32_t nr,
                const int32_t* r, double* out);

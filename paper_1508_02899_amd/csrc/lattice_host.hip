@@ -186,7 +186,7 @@ int lattice_init(const lattice_desc* d, lattice_t** out) {
       hipMalloc(&L->plane_sums, sizeof(double) * (size_t)L->nplanes) !=
           hipSuccess ||
       hipMalloc(&L->red, sizeof(double) * 8) != hipSuccess ||
-      hipHostMalloc((void**)&L->host_red, sizeof(double) * lat::kRhoMaxLevels,
+      hipHostMalloc((void**)&L->host_red, sizeof(double) * lat::kHostRed,
                     hipHostMallocDefault) != hipSuccess) {
     lattice_destroy(L);
     return LATTICE_ENOMEM;
@@ -628,6 +628,7 @@ int lattice_destroy(lattice_t* L) {
   if (L->plane_sums) (void)hipFree(L->plane_sums);
   if (L->red) (void)hipFree(L->red);
   if (L->obs_work) (void)hipFree(L->obs_work);
+  lat::s1_release(L);
   if (L->host_red) (void)hipHostFree(L->host_red);
   for (hipEvent_t e : L->ev) (void)hipEventDestroy(e);
   delete L;

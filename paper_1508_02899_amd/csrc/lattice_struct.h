@@ -21,8 +21,14 @@ struct lattice {
   int* flag = nullptr;          // sticky CFL / finiteness flag (device)
   double* plane_sums = nullptr; // nplanes doubles
   double* red = nullptr;        // 8 doubles: moments / absmax
-  double* host_red = nullptr;   // pinned: mirror of red, <rho_r^2> values
+  double* host_red = nullptr;   // pinned, kHostRed doubles
   double* obs_work = nullptr;   // lattice_rho_r2, from its first call on
+  // lattice_s1, from its first call on: the distance matrix (2D), rho and
+  // partial sums, the rocBLAS handle (2D)
+  void* s1_dist = nullptr;
+  double* s1_work = nullptr;
+  size_t s1_bytes = 0;
+  void* s1_blas = nullptr;
   char msg[512];
   // profiling
   bool prof = false;
@@ -36,6 +42,9 @@ struct lattice {
 };
 
 namespace lat {
+constexpr int kHostRed = 64;  // doubles read back through pinned memory
+// frees what lattice_s1 keeps (s1.hip)
+void s1_release(lattice_t* L);
 // learned correction pass (coarse_host.hip)
 hipError_t apply_mlp(lattice_t* L, void* f, const void* u, double dt,
                      double tau_p);
