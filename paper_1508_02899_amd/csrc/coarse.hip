@@ -585,272 +585,265 @@ __global__ __launch_bounds__(256) void k_flux_samples_nat(
 // lo = bf16(dz - hi), i.e. about 16 significant bits, so the products match
 // the FP32 arithmetic of the definition to ~2^-17 relative.
 //
-// A wavefront takes 32 samples at a time (two 16-sample column tiles).  The
-// forward and the backward-data products run transposed (units x samples,
-// as in the inference kernel): the 16x16 output tile of one layer, lane l
-// holding rows 4(l/16)+r, r < 4, of column l%16, is the B operand of the
-// next product once two tiles (rows u and u+16 of a 32-row K step) are
-// read as K indices 8(l/16)+i, i < 8 -- the weight operand is loaded in the
-// same K order.  The weight gradients sum over the samples (K = the 32
-// samples of the step): the activations and signals go through a
-// per-wavefront LDS transpose ([unit][sample], bf16).  Each wavefront writes
-// one row of per-parameter sums (then the block order reduction).
+// A block of four wavefronts takes 32 samples at a time (two 16-sample
+// column tiles t), wavefront m the units 16m .. 16m+15 of every layer: its
+// share of the weights is a quarter, and a minibatch of 8192 samples is 256
+// blocks, one per compute unit.  The step is a chain of latencies (weights,
+// layer, GELU, layer, GELU, output, and back), not a matter of rates: a
+// wavefront that took all 64 units of its 32 samples (64 blocks) needed
+// 20.2 us for 8192 samples, this split 8.8 us.
+//
+// The forward and the backward-data products run transposed (units x
+// samples): a 16x16 output tile holds, in lane l, rows (units) 4(l/16)+r,
+// r < 4, of column (sample) l%16.  The activations h1 and the signals dz
+// pass between the wavefronts through LDS in bf16, in two layouts:
+// [sample][unit], whose 16-byte pieces are the K-contiguous B operands of
+// the next layer, and [unit][sample] for the weight gradients, which sum
+// over the samples (K = the 32 samples of the step).  A block writes one
+// row of per-parameter sums (then the fixed-order reduction).
 
-constexpr int kGS = 32;                 // samples per wavefront step
-constexpr int kGP = kGS + 8;            // LDS row pitch (bf16), 80 bytes
-constexpr int kGWaves = 4;              // wavefronts per block
-// per wavefront: H1 / (X^T, 16 rows) and the hi / lo signals, [row][sample]
-constexpr int kGLds = (kNH + kNH + kNH + 16) * kGP;
+constexpr int kGS = 32;        // samples per block step
+constexpr int kGP = kGS + 8;   // pitch of [unit][sample] rows, 80 bytes
+constexpr int kGQ = kNH + 8;   // pitch of [sample][unit] rows, 144 bytes
 
-__global__ __launch_bounds__(64 * kGWaves) void k_mlp_grad_mfma(
+// Four floats as bf16 hi parts and the bf16 of what they leave.
+__device__ __forceinline__ void split4(const float (&d)[4], bf16x4* hi,
+                                       bf16x4* lo) {
+  *hi = pack4(d[0], d[1], d[2], d[3]);
+  float e[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) e[r] = d[r] - bf2f((uint16_t)(*hi)[r]);
+  *lo = pack4(e[0], e[1], e[2], e[3]);
+}
+// Eight floats as one bf16 operand.
+__device__ __forceinline__ s16x8 pack8(const float* v) {
+  return cat8(pack4(v[0], v[1], v[2], v[3]), pack4(v[4], v[5], v[6], v[7]));
+}
+
+__global__ __launch_bounds__(256) void k_mlp_grad_mfma(
     const float* __restrict__ P, const float* __restrict__ X,
     const float* __restrict__ T, const float* __restrict__ Wt, int64_t n,
     float inv_wsum, float* __restrict__ partial, int nrows) {
-  __shared__ __attribute__((aligned(16))) short lds[kGWaves * kGLds];
-  const int wv = (int)threadIdx.x >> 6;
-  const int row = (int)blockIdx.x * kGWaves + wv;  // partial row of this wave
-  if (row >= nrows) return;  // wave-uniform; no block barrier below
-  short* sH = lds + wv * kGLds;           // [64][kGP]: h1, later unused
-  short* sHi = sH + kNH * kGP;            // [64][kGP]: dz2 hi, then dz1 hi
-  short* sLo = sHi + kNH * kGP;           // [64][kGP]: dz2 lo, then dz1 lo
-  short* sX = sLo + kNH * kGP;            // [16][kGP]: x^T, row 8 = ones
+  __shared__ __attribute__((aligned(16))) short sH[kNH * kGP];  // h1
+  __shared__ __attribute__((aligned(16))) short sHt[kGS * kGQ];
+  __shared__ __attribute__((aligned(16))) short sD2[2][kNH * kGP];  // dz2
+  __shared__ __attribute__((aligned(16))) short sD2t[2][kGS * kGQ];
+  __shared__ __attribute__((aligned(16))) short sD1[2][kNH * kGP];  // dz1
+  // x^T, row 8 = ones (for the b1 gradient), rows 9..15 zeros; two buffers,
+  // since a wavefront may still read one when the next step fills the other
+  __shared__ __attribute__((aligned(16))) short sX[2][16 * kGP];
+  __shared__ float sY[4][kGS];  // the wavefronts' shares of the output
+  const int m = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int l = (int)threadIdx.x & 63;
   const int c = l & 15, g = l >> 4;
+  const int row = (int)blockIdx.x;
 
-  // ---- weights (bf16 as the network defines them) and biases
-  bf16x4 a1[4];          // W1^T, K = features 4g + r
-  s16x8 a2[4][2];        // W2^T: rows = output units, K = input units
-  s16x8 a2t[4][2];       // W2:   rows = input units,  K = output units
-  float w3q[4][4], b1r[4][4], b2r[4][4];
+  // ---- this wavefront's weights (bf16 as the network defines them), biases
+  bf16x4 a1;                // W1^T, K = features 4g + r
+  s16x8 a2[2], a2t[2];      // W2^T (rows = output units), W2 (input units)
+  float w3q[4], b1r[4], b2r[4];
+  {
+    float w[4], v2[2][8], v2t[2][8];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int k = 4 * g + r;
-      a1[u][r] = k < kNF ? bfs(P[kOffW1 + k * kNH + 16 * u + c]) : (short)0;
-      const int unit = 16 * u + 4 * g + r;
-      w3q[u][r] = qbf(P[kOffW3 + unit]);
-      b1r[u][r] = P[kOffB1 + unit];
-      b2r[u][r] = P[kOffB2 + unit];
-    }
+    for (int r = 0; r < 4; ++r)
+      w[r] = g < 2 ? P[kOffW1 + (4 * g + r) * kNH + 16 * m + c] : 0.f;
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int ku = kunit(kk, g, i);
-        a2[u][kk][i] = bfs(P[kOffW2 + ku * kNH + 16 * u + c]);
-        a2t[u][kk][i] = bfs(P[kOffW2 + (16 * u + c) * kNH + ku]);
+        const int k = 32 * kk + 8 * g + i;
+        v2[kk][i] = P[kOffW2 + k * kNH + 16 * m + c];
+        v2t[kk][i] = P[kOffW2 + (16 * m + c) * kNH + k];
       }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int unit = 16 * m + 4 * g + r;
+      w3q[r] = P[kOffW3 + unit];
+      b1r[r] = P[kOffB1 + unit];
+      b2r[r] = P[kOffB2 + unit];
+    }
+    a1 = pack4(w[0], w[1], w[2], w[3]);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      a2[kk] = pack8(v2[kk]);
+      a2t[kk] = pack8(v2t[kk]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w3q[r] = qbf(w3q[r]);
   }
   const float b3 = P[kOffB3];
-  // rows 8..15 of x^T: ones (row 8, for the b1 gradient) and zeros
-  for (int i = l; i < 8 * kGP; i += 64)
-    sX[8 * kGP + i] = (i < kGP) ? bfs(1.0f) : (short)0;
-
-  f32x4 gW2[4][4], gW1[4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    gW1[a] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int b = 0; b < 4; ++b) gW2[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = (int)threadIdx.x; i < 2 * 8 * kGP; i += 256) {
+    const int k = i % (8 * kGP);
+    sX[i / (8 * kGP)][8 * kGP + k] = k < kGP ? bfs(1.0f) : (short)0;
   }
-  float gb2[4][4] = {}, gw3[4][4] = {};
+
+  f32x4 gW2[4], gW1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int b = 0; b < 4; ++b) gW2[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float gb2[4] = {}, gw3[4] = {};
   float gb3 = 0.f, lsum = 0.f;
 
   const int64_t lo = n * row / nrows, hi = n * (row + 1) / nrows;
-  for (int64_t s0 = lo; s0 < hi; s0 += kGS) {
+  int buf = 0;
+  for (int64_t s0 = lo; s0 < hi; s0 += kGS, buf ^= 1) {
     // ---- inputs of the two column tiles (sample s0 + 16 t + c)
-    bf16x4 xb[2];
-    float tt[2], ww[2];
+    float tt[2], ww[2], gd1[2][4];
+    float xf[2][4] = {};
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int64_t i = s0 + 16 * t + c;
       const bool ok = i < hi;
-      float xf[4] = {0.f, 0.f, 0.f, 0.f};
       if (ok && g < 2)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) xf[r] = X[i * kNF + 4 * g + r];
+        for (int r = 0; r < 4; ++r) xf[t][r] = X[i * kNF + 4 * g + r];
       tt[t] = ok ? T[i] : 0.f;
       ww[t] = ok ? Wt[i] : 0.f;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        xb[t][r] = bfs(xf[r]);
-        if (g < 2) sX[(4 * g + r) * kGP + 16 * t + c] = xb[t][r];
-      }
     }
     // ---- layer 1 (K = 8 features, 16x16x16) and GELU
-    float gd1[4][2][4];
-    bf16x4 h1[4][2];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const f32x4 b = {b1r[u][0], b1r[u][1], b1r[u][2], b1r[u][3]};
-        const f32x4 z = mfma16(a1[u], xb[t], b);
-        float h[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float dg;
-          h[r] = gelu_d(z[r], &dg);
-          gd1[u][t][r] = dg;
-        }
-        h1[u][t] = pack4(h[0], h[1], h[2], h[3]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          sH[(16 * u + 4 * g + r) * kGP + 16 * t + c] = h1[u][t][r];
-      }
-    // ---- layer 2 (K = 64, 16x16x32) and GELU
-    float gd2[4][2][4], h2[4][2][4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        f32x4 z = {b2r[m][0], b2r[m][1], b2r[m][2], b2r[m][3]};
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-          z = mfma32(a2[m][kk], cat8(h1[2 * kk][t], h1[2 * kk + 1][t]), z);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float dg;
-          h2[m][t][r] = qbf(gelu_d(z[r], &dg));
-          gd2[m][t][r] = dg;
-        }
-      }
-    // ---- output, loss, dy (each sample's four lane groups agree)
-    float dy[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
+      const bf16x4 xb = pack4(xf[t][0], xf[t][1], xf[t][2], xf[t][3]);
+      if (m == 0 && g < 2)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          sX[buf][(4 * g + r) * kGP + 16 * t + c] = xb[r];
+      const f32x4 b = {b1r[0], b1r[1], b1r[2], b1r[3]};
+      const f32x4 z = mfma16(a1, xb, b);
+      float h[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) h[r] = gelu_d(z[r], &gd1[t][r]);
+      const bf16x4 hb = pack4(h[0], h[1], h[2], h[3]);
+      *(bf16x4*)(sHt + (16 * t + c) * kGQ + 16 * m + 4 * g) = hb;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        sH[(16 * m + 4 * g + r) * kGP + 16 * t + c] = hb[r];
+    }
+    __syncthreads();
+    // ---- layer 2 (K = 64, 16x16x32) and GELU; this wavefront's share of y
+    float gd2[2][4], h2[2][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      f32x4 z = {b2r[0], b2r[1], b2r[2], b2r[3]};
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+        z = mfma32(a2[kk],
+                   *(const s16x8*)(sHt + (16 * t + c) * kGQ + 32 * kk + 8 * g),
+                   z);
       float part = 0.f;
 #pragma unroll
-      for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) part += h2[m][t][r] * w3q[m][r];
+      for (int r = 0; r < 4; ++r) {
+        h2[t][r] = qbf(gelu_d(z[r], &gd2[t][r]));
+        part += h2[t][r] * w3q[r];
+      }
       part += __shfl_xor(part, 16);
       part += __shfl_xor(part, 32);
-      const float y = b3 + part;
+      if (g == 0) sY[m][16 * t + c] = part;
+    }
+    __syncthreads();
+    // ---- output, loss, dy; backward through layer 3 and the second GELU
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int q = 16 * t + c;
+      const float y = b3 + ((sY[0][q] + sY[1][q]) + (sY[2][q] + sY[3][q]));
       const float e = y - tt[t];
+      const float dy = 2.0f * ww[t] * e * inv_wsum;
       if (g == 0) {
         lsum += ww[t] * e * e * inv_wsum;
+        gb3 += dy;
       }
-      dy[t] = 2.0f * ww[t] * e * inv_wsum;
-      if (g == 0) gb3 += dy[t];
-    }
-    // ---- backward through layer 3 and the second GELU
-    s16x8 dhi[4][2], dlo[4][2];  // dz2 as K operands: [K step][t] below
-    float dz2[4][2][4];
+      float d[4];
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+      for (int r = 0; r < 4; ++r) {
+        d[r] = w3q[r] * dy * gd2[t][r];
+        gb2[r] += d[r];
+        gw3[r] += h2[t][r] * dy;
+      }
+      bf16x4 dv[2];
+      split4(d, &dv[0], &dv[1]);
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int p = 0; p < 2; ++p) {
+        *(bf16x4*)(sD2t[p] + (16 * t + c) * kGQ + 16 * m + 4 * g) = dv[p];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float d = w3q[m][r] * dy[t] * gd2[m][t][r];
-          dz2[m][t][r] = d;
-          gb2[m][r] += d;
-          gw3[m][r] += h2[m][t][r] * dy[t];
-          const short hs = bfs(d);
-          const short ls = bfs(d - bf2f((uint16_t)hs));
-          sHi[(16 * m + 4 * g + r) * kGP + 16 * t + c] = hs;
-          sLo[(16 * m + 4 * g + r) * kGP + 16 * t + c] = ls;
-        }
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float d = dz2[2 * kk + (i >> 2)][t][i & 3];
-          const short hs = bfs(d);
-          dhi[kk][t][i] = hs;
-          dlo[kk][t][i] = bfs(d - bf2f((uint16_t)hs));
-        }
-    // ---- weight gradient of layer 2: sum over the 32 samples
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const s16x8 ah = *(const s16x8*)(sH + (16 * a + c) * kGP + 8 * g);
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const s16x8 bh = *(const s16x8*)(sHi + (16 * b + c) * kGP + 8 * g);
-        const s16x8 bl = *(const s16x8*)(sLo + (16 * b + c) * kGP + 8 * g);
-        gW2[a][b] = mfma32(ah, bh, gW2[a][b]);
-        gW2[a][b] = mfma32(ah, bl, gW2[a][b]);
+        for (int r = 0; r < 4; ++r)
+          sD2[p][(16 * m + 4 * g + r) * kGP + 16 * t + c] = dv[p][r];
       }
     }
-    // ---- backward through layer 2 (K = 64 output units) and the first GELU
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    __syncthreads();
+    // ---- backward through layer 2 (K = 64 output units), the first GELU
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+    for (int t = 0; t < 2; ++t) {
+      f32x4 dh = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        f32x4 dh = {0.f, 0.f, 0.f, 0.f};
+      for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-          dh = mfma32(a2t[m][kk], dhi[kk][t], dh);
-          dh = mfma32(a2t[m][kk], dlo[kk][t], dh);
-        }
+        for (int p = 0; p < 2; ++p)
+          dh = mfma32(a2t[kk],
+                      *(const s16x8*)(sD2t[p] + (16 * t + c) * kGQ + 32 * kk +
+                                      8 * g),
+                      dh);
+      float d[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float d = dh[r] * gd1[m][t][r];
-          const short hs = bfs(d);
-          sHi[(16 * m + 4 * g + r) * kGP + 16 * t + c] = hs;
-          sLo[(16 * m + 4 * g + r) * kGP + 16 * t + c] =
-              bfs(d - bf2f((uint16_t)hs));
-        }
-      }
-    // ---- weight gradient of layer 1 (rows: 8 features, ones, zeros)
+      for (int r = 0; r < 4; ++r) d[r] = dh[r] * gd1[t][r];
+      bf16x4 dv[2];
+      split4(d, &dv[0], &dv[1]);
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          sD1[p][(16 * m + 4 * g + r) * kGP + 16 * t + c] = dv[p][r];
+    }
+    // ---- weight gradient of layer 2 (rows: this wavefront's input units)
+    {
+      const s16x8 ah = *(const s16x8*)(sH + (16 * m + c) * kGP + 8 * g);
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+          gW2[b] = mfma32(
+              ah, *(const s16x8*)(sD2[p] + (16 * b + c) * kGP + 8 * g),
+              gW2[b]);
+    }
+    // ---- weight gradient of layer 1 (rows: 8 features, ones, zeros);
+    // sD1's rows are this wavefront's own
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
     {
-      const s16x8 ax = *(const s16x8*)(sX + c * kGP + 8 * g);
+      const s16x8 ax = *(const s16x8*)(sX[buf] + c * kGP + 8 * g);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const s16x8 bh = *(const s16x8*)(sHi + (16 * b + c) * kGP + 8 * g);
-        const s16x8 bl = *(const s16x8*)(sLo + (16 * b + c) * kGP + 8 * g);
-        gW1[b] = mfma32(ax, bh, gW1[b]);
-        gW1[b] = mfma32(ax, bl, gW1[b]);
-      }
+      for (int p = 0; p < 2; ++p)
+        gW1 = mfma32(ax,
+                     *(const s16x8*)(sD1[p] + (16 * m + c) * kGP + 8 * g),
+                     gW1);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
   }
 
-  // ---- this wavefront's row of per-parameter sums
+  // ---- this block's row of per-parameter sums
   float* out = partial + (size_t)row * (kNParams + 1);
 #pragma unroll
-  for (int b = 0; b < 4; ++b)
+  for (int r = 0; r < 4; ++r) {
+    const int k = 4 * g + r;
+    if (k < kNF) out[kOffW1 + k * kNH + 16 * m + c] = gW1[r];
+    if (k == kNF) out[kOffB1 + 16 * m + c] = gW1[r];  // the ones row
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int k = 4 * g + r, j = 16 * b + c;
-      if (k < kNF) out[kOffW1 + k * kNH + j] = gW1[b][r];
-      if (k == kNF) out[kOffB1 + j] = gW1[b][r];   // the ones row
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-        out[kOffW2 + (16 * a + 4 * g + r) * kNH + j] = gW2[a][b][r];
-    }
+    for (int b = 0; b < 4; ++b)
+      out[kOffW2 + (16 * m + k) * kNH + 16 * b + c] = gW2[b][r];
+  }
   // per-unit sums over the 16 sample lanes of each lane group
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int r = 0; r < 4; ++r) {
+    float sb = gb2[r], sw = gw3[r];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      float sb = gb2[m][r], sw = gw3[m][r];
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) {
-        sb += __shfl_xor(sb, o);
-        sw += __shfl_xor(sw, o);
-      }
-      if (c == 0) {
-        out[kOffB2 + 16 * m + 4 * g + r] = sb;
-        out[kOffW3 + 16 * m + 4 * g + r] = sw;
-      }
+    for (int o = 1; o < 16; o <<= 1) {
+      sb += __shfl_xor(sb, o);
+      sw += __shfl_xor(sw, o);
     }
+    if (c == 0) {
+      out[kOffB2 + 16 * m + 4 * g + r] = sb;
+      out[kOffW3 + 16 * m + 4 * g + r] = sw;
+    }
+  }
+  if (m != 0) return;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
     gb3 += __shfl_xor(gb3, o);
@@ -863,53 +856,112 @@ __global__ __launch_bounds__(64 * kGWaves) void k_mlp_grad_mfma(
 }
 
 // Sum of the partial rows, fixed order: a block takes 64 consecutive
-// entries (coalesced row reads); its eight wavefronts sum rows q, q+8, ...
-// (q = wavefront) and the eight sums are added pairwise in a fixed order.
-// With adam_step > 0 the Adam update (Kingma & Ba 2015) of those
-// parameters follows at once.
-constexpr int kRedWaves = 8;
+// entries (coalesced row reads); its 16 wavefronts sum rows q, q+16, ...
+// (q = wavefront), 16 rows' loads in flight, and the sums are added pairwise.
+// With bc1 > 0 the Adam update (Kingma & Ba 2015) of those parameters
+// follows at once; bc1 = 1 - b1^t and bc2 = 1 - b2^t come from the host in
+// double, where 1 - b2^t does not cancel.  A latency chain (load, tree,
+// update): 256 rows 3.4 us, with eight wavefronts, the moments loaded after
+// the sum and powf 6.35 us.
+constexpr int kRedWaves = 16;
 __global__ __launch_bounds__(64 * kRedWaves) void k_grad_reduce(
     const float* __restrict__ partial, int nrows, float* __restrict__ grad,
     float* __restrict__ loss, float* __restrict__ P, float* __restrict__ m,
-    float* __restrict__ v, int adam_step, float lr, float b1, float b2,
+    float* __restrict__ v, float bc1, float bc2, float lr, float b1, float b2,
     float eps) {
   __shared__ float sh[kRedWaves][64];
   const int q = (int)threadIdx.x >> 6, j = (int)threadIdx.x & 63;
   const int p = (int)blockIdx.x * 64 + j;
+  const bool adam = bc1 > 0.f && q == 0 && p < kNParams;
+  float m0 = 0.f, v0 = 0.f, p0 = 0.f;
+  if (adam) {
+    m0 = m[p];
+    v0 = v[p];
+    p0 = P[p];
+  }
   float s = 0.f;
   if (p <= kNParams) {
-    // the loads of eight rows in flight together, added in row order
     const float* col = partial + p;
-    const size_t rs = (size_t)kRedWaves * (kNParams + 1);
-    int r = q;
-    for (; r + 7 * kRedWaves < nrows; r += 8 * kRedWaves) {
-      float v[8];
+    constexpr int U = 16;
+    for (int r = q; r < nrows; r += U * kRedWaves) {
+      float x[U];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = col[(size_t)r * (kNParams + 1) + k * rs];
+      for (int k = 0; k < U; ++k) {
+        const int rr = r + k * kRedWaves;
+        x[k] = rr < nrows ? col[(size_t)rr * (kNParams + 1)] : 0.f;
+      }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) s += v[k];
+      for (int k = 0; k < U; ++k) s += x[k];
     }
-    for (; r < nrows; r += kRedWaves) s += col[(size_t)r * (kNParams + 1)];
   }
   sh[q][j] = s;
   __syncthreads();
   if (q != 0 || p > kNParams) return;
-  const float gi = ((sh[0][j] + sh[1][j]) + (sh[2][j] + sh[3][j])) +
-                   ((sh[4][j] + sh[5][j]) + (sh[6][j] + sh[7][j]));
+  float x[kRedWaves];
+#pragma unroll
+  for (int k = 0; k < kRedWaves; ++k) x[k] = sh[k][j];
+#pragma unroll
+  for (int w = 1; w < kRedWaves; w <<= 1)
+#pragma unroll
+    for (int k = 0; k < kRedWaves; k += 2 * w) x[k] += x[k + w];
+  const float gi = x[0];
   if (p == kNParams) {
     loss[0] = gi;
     return;
   }
   grad[p] = gi;
-  if (adam_step > 0) {
-    const float mi = b1 * m[p] + (1.f - b1) * gi;
-    const float vi = b2 * v[p] + (1.f - b2) * gi * gi;
+  if (adam) {
+    const float mi = b1 * m0 + (1.f - b1) * gi;
+    const float vi = b2 * v0 + (1.f - b2) * gi * gi;
     m[p] = mi;
     v[p] = vi;
-    const float mh = mi / (1.f - powf(b1, (float)adam_step));
-    const float vh = vi / (1.f - powf(b2, (float)adam_step));
-    P[p] -= lr * mh / (sqrtf(vh) + eps);
+    const float mh = mi / bc1;
+    const float vh = vi / bc2;
+    P[p] = p0 - lr * mh / (sqrtf(vh) + eps);
   }
+}
+
+// Sum of n floats in FP64, fixed order: block b takes values b 256 + t + k
+// 256 gridDim, one partial per block; then one block adds the partials.
+__global__ __launch_bounds__(256) void k_sum_part(const float* __restrict__ w,
+                                                  int64_t n,
+                                                  double* __restrict__ part) {
+  __shared__ double sh[4];
+  double a = 0.0;
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  for (; i + 7 * stride < n; i += 8 * stride) {
+    float x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = w[i + k * stride];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a += (double)x[k];
+  }
+  for (; i < n; i += stride) a += (double)w[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    part[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+__global__ __launch_bounds__(256) void k_sum_final(
+    const double* __restrict__ part, int np, double* __restrict__ out) {
+  __shared__ double sh[4];
+  double a = 0.0;
+  for (int i = threadIdx.x; i < np; i += 256) a += part[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
+  __syncthreads();
+  if (threadIdx.x == 0) out[0] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+__global__ __launch_bounds__(256) void k_zero2(float* __restrict__ a,
+                                               float* __restrict__ b, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) a[i] = b[i] = 0.f;
 }
 
 __global__ __launch_bounds__(256) void k_pack_bf16(const float* __restrict__ P,
@@ -1189,10 +1241,7 @@ hipError_t launch_flux_samples_natural(
   return hipGetLastError();
 }
 
-// one 32-sample step per wavefront at least: a minibatch of 8192 samples
-// is then 256 wavefronts (64 workgroups), 19.5 us; with two steps per
-// wavefront the grid halves and the pass takes 25.5 us, more than the
-// summation of the extra partial rows saves
+// a row (a block) per 32-sample step, as far as the rows go
 int mlp_grad_rows(int64_t n, int max_rows) {
   int64_t r = (n + kGS - 1) / kGS;
   if (r > max_rows) r = max_rows;
@@ -1203,9 +1252,8 @@ hipError_t launch_mlp_grad_mfma(const float* params, const float* X,
                                 const float* t, const float* w, int64_t n,
                                 double wsum, float* partial, int nrows,
                                 hipStream_t s) {
-  const int blocks = (nrows + kGWaves - 1) / kGWaves;
-  hipLaunchKernelGGL(k_mlp_grad_mfma, dim3(blocks), dim3(64 * kGWaves), 0, s,
-                     params, X, t, w, n, (float)(1.0 / wsum), partial, nrows);
+  hipLaunchKernelGGL(k_mlp_grad_mfma, dim3(nrows), dim3(256), 0, s, params, X,
+                     t, w, n, (float)(1.0 / wsum), partial, nrows);
   return hipGetLastError();
 }
 
@@ -1214,7 +1262,8 @@ hipError_t launch_grad_reduce(const float* partial, int nrows, float* grad,
   hipLaunchKernelGGL(k_grad_reduce, dim3((kNParams + 1 + 63) / 64),
                      dim3(64 * kRedWaves), 0, s, partial, nrows, grad, loss,
                      (float*)nullptr,
-                     (float*)nullptr, (float*)nullptr, 0, 0.f, 0.f, 0.f, 0.f);
+                     (float*)nullptr, (float*)nullptr, 0.f, 0.f, 0.f, 0.f, 0.f,
+                     0.f);
   return hipGetLastError();
 }
 
@@ -1225,7 +1274,24 @@ hipError_t launch_grad_reduce_adam(const float* partial, int nrows,
                                    hipStream_t s) {
   hipLaunchKernelGGL(k_grad_reduce, dim3((kNParams + 1 + 63) / 64),
                      dim3(64 * kRedWaves), 0, s, partial, nrows, grad, loss,
-                     params, m, v, step, lr, b1, b2, eps);
+                     params, m, v, (float)(1.0 - pow((double)b1, step)),
+                     (float)(1.0 - pow((double)b2, step)), lr, b1, b2, eps);
+  return hipGetLastError();
+}
+
+hipError_t launch_sum(const float* w, int64_t n, double* work,
+                      hipStream_t s) {
+  int64_t g = (n + 256 * 8 - 1) / (256 * 8);
+  g = g > kSumParts ? kSumParts : g;
+  hipLaunchKernelGGL(k_sum_part, dim3((unsigned)g), dim3(256), 0, s, w, n,
+                     work + 1);
+  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, s, work + 1, (int)g,
+                     work);
+  return hipGetLastError();
+}
+
+hipError_t launch_zero2(float* a, float* b, int n, hipStream_t s) {
+  hipLaunchKernelGGL(k_zero2, dim3((n + 255) / 256), dim3(256), 0, s, a, b, n);
   return hipGetLastError();
 }
 

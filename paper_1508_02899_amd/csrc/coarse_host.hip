@@ -5,7 +5,6 @@
 #include <string.h>
 
 #include <new>
-#include <vector>
 
 #include "../../include/lattice.h"
 #include "coarse_internal.h"
@@ -23,7 +22,13 @@ struct lattice_mlp {
   float* partial = nullptr;   // nblocks x (kNParams + 1)
   int max_blocks = 256;
   int adam_t = 0;
-  float* host_loss = nullptr;  // pinned
+  double* sum_work = nullptr;  // sum of the sample weights
+  // pinned: the sum, a loss, a set of parameters on its way
+  struct Host {
+    double sum;
+    float loss;
+    float params[lat::kNParams];
+  }* host = nullptr;
 };
 
 namespace {
@@ -32,20 +37,17 @@ hipError_t mlp_sync_bf16(lattice_mlp_t* M) {
   return lat::launch_pack_bf16(M->params, M->wq, M->stream);
 }
 
-// sum of w[0..n) on the device (one-off, synchronous)
-hipError_t device_sum(const float* w, int64_t n, hipStream_t s, double* out) {
-  std::vector<float> h((size_t)n);
-  hipError_t e = hipMemcpyAsync(h.data(), w, sizeof(float) * n,
-                                hipMemcpyDeviceToHost, s);
-  if (e != hipSuccess) return e;
-  e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return e;
-  double acc = 0.0;
-  for (float x : h) acc += x;
-  *out = acc;
-  return hipSuccess;
+// sum of w[0..n) (synchronous)
+hipError_t device_sum(lattice_mlp_t* M, const float* w, int64_t n,
+                      double* out) {
+  hipError_t e = lat::launch_sum(w, n, M->sum_work, M->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(&M->host->sum, M->sum_work, sizeof(double),
+                       hipMemcpyDeviceToHost, M->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(M->stream);
+  *out = M->host->sum;
+  return e;
 }
-
 
 }  // namespace
 
@@ -77,18 +79,15 @@ int lattice_mlp_create(void* stream, lattice_mlp_t** out) {
       hipMalloc(&M->loss, sizeof(float)) != hipSuccess ||
       hipMalloc(&M->partial,
                 sizeof(float) * (np + 1) * M->max_blocks) != hipSuccess ||
-      hipHostMalloc((void**)&M->host_loss, sizeof(float),
+      hipMalloc(&M->sum_work, sizeof(double) * (lat::kSumParts + 1)) !=
+          hipSuccess ||
+      hipHostMalloc((void**)&M->host, sizeof(*M->host),
                     hipHostMallocDefault) != hipSuccess) {
     lattice_mlp_destroy(M);
     return LATTICE_ENOMEM;
   }
-  std::vector<float> zero(np, 0.f);
-  if (hipMemcpy(M->params, zero.data(), sizeof(float) * np,
-                hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(M->m, zero.data(), sizeof(float) * np,
-                hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(M->v, zero.data(), sizeof(float) * np,
-                hipMemcpyHostToDevice) != hipSuccess ||
+  if (lat::launch_zero2(M->params, M->m, (int)np, M->stream) != hipSuccess ||
+      lat::launch_zero2(M->grad, M->v, (int)np, M->stream) != hipSuccess ||
       mlp_sync_bf16(M) != hipSuccess ||
       hipStreamSynchronize(M->stream) != hipSuccess) {
     lattice_mlp_destroy(M);
@@ -100,27 +99,26 @@ int lattice_mlp_create(void* stream, lattice_mlp_t** out) {
 
 int lattice_mlp_set_params(lattice_mlp_t* M, const float* host_params) {
   if (!M || !host_params) return LATTICE_EINVAL;
-  if (hipMemcpyAsync(M->params, host_params, sizeof(float) * lat::kNParams,
-                     hipMemcpyHostToDevice, M->stream) != hipSuccess ||
+  memcpy(M->host->params, host_params, sizeof(float) * lat::kNParams);
+  if (hipMemcpyAsync(M->params, M->host->params,
+                     sizeof(float) * lat::kNParams, hipMemcpyHostToDevice,
+                     M->stream) != hipSuccess ||
       mlp_sync_bf16(M) != hipSuccess ||
+      lat::launch_zero2(M->m, M->v, lat::kNParams, M->stream) != hipSuccess ||
       hipStreamSynchronize(M->stream) != hipSuccess)
     return LATTICE_EHIP;
   M->adam_t = 0;
-  std::vector<float> zero(lat::kNParams, 0.f);
-  if (hipMemcpy(M->m, zero.data(), sizeof(float) * lat::kNParams,
-                hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(M->v, zero.data(), sizeof(float) * lat::kNParams,
-                hipMemcpyHostToDevice) != hipSuccess)
-    return LATTICE_EHIP;
   return LATTICE_OK;
 }
 
 int lattice_mlp_get_params(lattice_mlp_t* M, float* host_params) {
   if (!M || !host_params) return LATTICE_EINVAL;
-  if (hipMemcpyAsync(host_params, M->params, sizeof(float) * lat::kNParams,
-                     hipMemcpyDeviceToHost, M->stream) != hipSuccess ||
+  if (hipMemcpyAsync(M->host->params, M->params,
+                     sizeof(float) * lat::kNParams, hipMemcpyDeviceToHost,
+                     M->stream) != hipSuccess ||
       hipStreamSynchronize(M->stream) != hipSuccess)
     return LATTICE_EHIP;
+  memcpy(host_params, M->host->params, sizeof(float) * lat::kNParams);
   return LATTICE_OK;
 }
 
@@ -204,7 +202,7 @@ int lattice_mlp_grad(lattice_mlp_t* M, const float* X, const float* t,
                      const float* w, int64_t n, float* grad, double* loss) {
   if (!M || !X || !t || !w || n < 1) return LATTICE_EINVAL;
   double ws = 0.0;
-  if (device_sum(w, n, M->stream, &ws) != hipSuccess) return LATTICE_EHIP;
+  if (device_sum(M, w, n, &ws) != hipSuccess) return LATTICE_EHIP;
   if (!(ws > 0)) return LATTICE_EINVAL;
   const int nr = lat::mlp_grad_rows(n, M->max_blocks);
   if (lat::launch_mlp_grad_mfma(M->params, X, t, w, n, ws, M->partial, nr,
@@ -215,11 +213,11 @@ int lattice_mlp_grad(lattice_mlp_t* M, const float* X, const float* t,
   if (grad && hipMemcpyAsync(grad, M->grad, sizeof(float) * lat::kNParams,
                              hipMemcpyDeviceToDevice, M->stream) != hipSuccess)
     return LATTICE_EHIP;
-  if (hipMemcpyAsync(M->host_loss, M->loss, sizeof(float),
+  if (hipMemcpyAsync(&M->host->loss, M->loss, sizeof(float),
                      hipMemcpyDeviceToHost, M->stream) != hipSuccess ||
       hipStreamSynchronize(M->stream) != hipSuccess)
     return LATTICE_EHIP;
-  if (loss) *loss = *M->host_loss;
+  if (loss) *loss = M->host->loss;
   return LATTICE_OK;
 }
 
@@ -231,7 +229,7 @@ int lattice_mlp_train(lattice_mlp_t* M, const float* X, const float* t,
     return LATTICE_EINVAL;
   if (batch > n) batch = n;
   double ws = 0.0;
-  if (device_sum(w, n, M->stream, &ws) != hipSuccess) return LATTICE_EHIP;
+  if (device_sum(M, w, n, &ws) != hipSuccess) return LATTICE_EHIP;
   if (!(ws > 0)) return LATTICE_EINVAL;
   // loss of a minibatch = sum w e^2 / (batch * mean w)
   const double norm = (double)batch * (ws / (double)n);
@@ -249,11 +247,11 @@ int lattice_mlp_train(lattice_mlp_t* M, const float* X, const float* t,
       return LATTICE_EHIP;
   }
   if (mlp_sync_bf16(M) != hipSuccess) return LATTICE_EHIP;
-  if (hipMemcpyAsync(M->host_loss, M->loss, sizeof(float),
+  if (hipMemcpyAsync(&M->host->loss, M->loss, sizeof(float),
                      hipMemcpyDeviceToHost, M->stream) != hipSuccess ||
       hipStreamSynchronize(M->stream) != hipSuccess)
     return LATTICE_EHIP;
-  if (final_loss) *final_loss = *M->host_loss;
+  if (final_loss) *final_loss = M->host->loss;
   return LATTICE_OK;
 }
 
@@ -293,7 +291,8 @@ int lattice_mlp_destroy(lattice_mlp_t* M) {
   if (M->v) (void)hipFree(M->v);
   if (M->loss) (void)hipFree(M->loss);
   if (M->partial) (void)hipFree(M->partial);
-  if (M->host_loss) (void)hipHostFree(M->host_loss);
+  if (M->sum_work) (void)hipFree(M->sum_work);
+  if (M->host) (void)hipHostFree(M->host);
   delete M;
   return LATTICE_OK;
 }

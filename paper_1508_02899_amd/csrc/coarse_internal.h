@@ -63,9 +63,9 @@ hipError_t launch_flux_samples_natural(
     const float* f_pred, const float* u, const int32_t* sites, int nsites,
     float* X, float* t, float* w, hipStream_t s);
 
-// Per-wavefront partial sums of the loss gradient (matrix cores): nrows
-// rows of kNParams + 1 floats (gradient, then the row's loss sum), one per
-// wavefront; mlp_grad_rows gives the row count for n samples (at most
+// Partial sums of the loss gradient (matrix cores): nrows rows of
+// kNParams + 1 floats (gradient, then the row's loss sum), one per block;
+// mlp_grad_rows gives the row count for n samples (at most
 // max_rows).
 int mlp_grad_rows(int64_t n, int max_rows);
 hipError_t launch_mlp_grad_mfma(const float* params, const float* X,
@@ -81,6 +81,11 @@ hipError_t launch_grad_reduce_adam(const float* partial, int nrows,
                                    hipStream_t s);
 hipError_t launch_grad_reduce(const float* partial, int nrows, float* grad,
                               float* loss, hipStream_t s);
+// work[0] = sum of w[0..n) in FP64, fixed order; work: kSumParts + 1 doubles.
+constexpr int kSumParts = 1024;
+hipError_t launch_sum(const float* w, int64_t n, double* work, hipStream_t s);
+// a[0..n) = b[0..n) = 0.
+hipError_t launch_zero2(float* a, float* b, int n, hipStream_t s);
 // bf16 copies of the weights for the matrix-core forward pass.
 hipError_t launch_pack_bf16(const float* params, uint16_t* wq, hipStream_t s);
 

@@ -118,6 +118,39 @@ def test_mlp_gradient_matches_oracle():
     m.close()
 
 
+@pytest.mark.parametrize("n", [1, 31, 33, 63, 8191, 8193, 20011])
+def test_mlp_gradient_rows_and_remainders(n):
+    """One block with a remainder up to several 32-sample steps per block
+    (256 rows at most), against the oracle.  Tolerance: an activation that
+    FP32 and FP64 round to different bf16 values moves one of 64 terms by
+    2^-8, rare enough (5e-5 per activation) to count once at small n and to
+    average out at large n."""
+    import torch
+    from oracle import coarse as C
+    from paper_1508_02899_amd import Mlp
+    rng = np.random.default_rng(330 + n)
+    P = _params(rng, 1.2)
+    X = rng.standard_normal((n, 8)).astype(np.float32)
+    X[:, 7] = 0.0
+    t = rng.standard_normal(n).astype(np.float32)
+    w = (rng.random(n) + 0.1).astype(np.float32)
+    w[n // 2 + 1:n // 2 + 5] = 0.0
+    m = Mlp()
+    m.set_params(_pack(P))
+    d = [torch.from_numpy(a).cuda() for a in (X, t, w)]
+    loss, g = m.grad(*d)
+    L, go = C.loss_and_grads(_unpack(_pack(P)), X.astype(np.float64),
+                             t.astype(np.float64), w.astype(np.float64))
+    err = rel_l2(g.cpu().numpy(), _pack(go))
+    say(f"  n {n}: gradient rel L2 {err:.2e}")
+    tol = 2.0 ** -8 if n < 100 else 1e-4
+    assert loss == pytest.approx(L, rel=tol)
+    assert err < tol
+    l2, g2 = m.grad(*d)
+    assert l2 == loss and torch.equal(g, g2)
+    m.close()
+
+
 def test_adam_training_reduces_loss_on_teacher_targets():
     """Targets from a random 'teacher' network: Adam on the GPU must cut the
     loss of a differently initialised student by 10x."""
