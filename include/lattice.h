@@ -317,7 +317,8 @@ int lattice_copy_state(lattice_t* L, void* dst, const void* src);
 int lattice_sync(lattice_t* L);
 
 /* Per-launch timing of the streaming/collision kernels with HIP events on
- * the handle's stream.  enable != 0 starts recording (and resets the
+ * the handle's stream.  While it is on, every step of a short 1D lattice is
+ * a launch of its own (otherwise one launch takes several steps).  enable != 0 starts recording (and resets the
  * totals); lattice_profile_read waits for the stream and returns the summed
  * kernel time in milliseconds and the number of timed launches. */
 int lattice_profile(lattice_t* L, int enable);

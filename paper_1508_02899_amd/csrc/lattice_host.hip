@@ -295,8 +295,20 @@ static int run_call(const lattice_desc& d, CallPlan& p, void* f,
                                  d.dtype == LATTICE_F64, flag, st),
            "cfl check launch"))
     return LATTICE_EHIP;
+  // Short 1D lattices: several steps per launch, spread evenly over an even
+  // number of launches (no copy needed) unless there is only one step;
+  // profiled runs time every step by itself.
+  int64_t launches = p.passes;
+  if (d.dim == 1 && stream && nsteps > 1 && !(L && L->prof)) {
+    const int64_t most =
+        lat::step1d_multi_steps(d.nv, d.nx, d.vstride, d.nsub, p.a.f64);
+    if (most > 1) {
+      launches = (nsteps + most - 1) / most;
+      launches += launches & 1;
+    }
+  }
   void* bufs[2];
-  if (p.passes % 2 == 0) {
+  if (launches % 2 == 0) {
     bufs[0] = f;
     bufs[1] = twin;
   } else {
@@ -307,6 +319,20 @@ static int run_call(const lattice_desc& d, CallPlan& p, void* f,
   }
   lat::StepArgs& a = p.a;
   a.flag = flag;
+  if (launches < p.passes) {
+    a.u = u;
+    a.shift = d.vstride;
+    for (int64_t k = 0, s = 0; k < launches; ++k) {
+      const int64_t n = (nsteps - s + launches - k - 1) / (launches - k);
+      a.fin = bufs[k & 1];
+      a.fout = bufs[(k + 1) & 1];
+      if (!chk(lat::launch_step1d_multi(a, (int)n, s, d.u_hold, st),
+               "step kernel launch"))
+        return LATTICE_EHIP;
+      s += n;
+    }
+    return LATTICE_OK;
+  }
   int64_t k = 0;
   for (int64_t s = 0; s < nsteps; ++s) {
     const int64_t sl = d.u_hold > 0 ? s / d.u_hold : 0;

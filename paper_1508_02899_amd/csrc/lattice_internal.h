@@ -42,6 +42,13 @@ hipError_t launch_step1d(const StepArgs& a, hipStream_t s);
 // is compiled for; launch_step1d picks it for short lattices.
 bool step1d_parts_supported(int nv, int f64);
 hipError_t launch_step1d_parts(const StepArgs& a, hipStream_t s);
+// Several steps per launch for short 1D lattices (step1d_multi.hip): the
+// most steps one launch may take (1: the one-step passes are used), and the
+// launch of steps step0 .. step0 + nsteps - 1 of a call; a.u is slice 0.
+constexpr int64_t kMultiSmall = 32 * 256;  // 32-site tiles, one per CU
+int step1d_multi_steps(int nv, int64_t nx, int shift, int nsub, int f64);
+hipError_t launch_step1d_multi(const StepArgs& a, int nsteps, int64_t step0,
+                               int64_t u_hold, hipStream_t s);
 hipError_t launch_step2d(const StepArgs& a, hipStream_t s);
 
 // Sticky CFL / finiteness check of the u slices: sets flag |= 1 when some

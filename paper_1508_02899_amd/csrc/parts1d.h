@@ -160,22 +160,18 @@ struct Parts1DTile {
     return u[min(x0 + lane_site(), nx - 1)] * alpha_scale;
   }
 
-  // 2b. nsub x [drift, diffusion] on every column of the tile, in place.
-  // A site's column belongs to one wavefront, so no other wavefront
-  // touches it (no barrier needed between the read and the write-back).
+  // 2b. nsub x [drift, diffusion] on this lane's cells c of its site's
+  // column (part p of the lane), the halo cells and the end faces taken from
+  // the neighbouring lanes.
   template <bool KOREN>
-  __device__ __forceinline__ static void collide(T* __restrict__ tile,
-                                                 T alpha, int nsub, T beta,
-                                                 T D) {
+  __device__ __forceinline__ static void update(T (&c)[W], T alpha, int nsub,
+                                                T beta, T D) {
 #pragma clang fp contract(off)
     const int lane = (int)threadIdx.x & 63;
     const int p = lane / S;
     const bool first = p == 0, last = p == P - 1;
     const int lane_l = lane - S, lane_r = lane + S;
     const int j0 = p * (W - 1);
-    T* col = tile + j0 * STRIDE + p * SKEW + lane_site();  // = row(j0 + i)
-    // for i < W-1; the part's last cell lies in the next block
-
     T nup[W + 2], num[W + 2];  // split coefficients of cells -1 .. W
 #pragma unroll
     for (int i = 0; i < W + 2; ++i) {
@@ -183,11 +179,6 @@ struct Parts1DTile {
       nup[i] = pos(nu);
       num[i] = neg(nu);
     }
-    T c[W];
-#pragma unroll
-    for (int i = 0; i < W - 1; ++i) c[i] = col[i * STRIDE];
-    c[W - 1] = col[(W - 1) * STRIDE + SKEW];
-
 #pragma unroll 1
     for (int sub = 0; sub < nsub; ++sub) {
       // drift: cells -1 .. W (the outer cells from the neighbouring parts,
@@ -246,9 +237,27 @@ struct Parts1DTile {
 #pragma unroll
       for (int i = 0; i < W; ++i) c[i] = fma_t(D, df[i] - df[i + 1], q[i]);
     }
+  }
+
+  // 2c. the update of every column of the tile, in place.
+  // A site's column belongs to one wavefront, so no other wavefront
+  // touches it (no barrier needed between the read and the write-back).
+  template <bool KOREN>
+  __device__ __forceinline__ static void collide(T* __restrict__ tile,
+                                                 T alpha, int nsub, T beta,
+                                                 T D) {
+    const int p = ((int)threadIdx.x & 63) / S;
+    T* col = tile + p * (W - 1) * STRIDE + p * SKEW +
+             lane_site();  // = row(p (W - 1) + i)
+    // for i < W-1; the part's last cell lies in the next block
+    T c[W];
+#pragma unroll
+    for (int i = 0; i < W - 1; ++i) c[i] = col[i * STRIDE];
+    c[W - 1] = col[(W - 1) * STRIDE + SKEW];
+    update<KOREN>(c, alpha, nsub, beta, D);
 #pragma unroll
     for (int i = 0; i < W - 1; ++i) col[i * STRIDE] = c[i];
-    if (last) col[(W - 1) * STRIDE + SKEW] = c[W - 1];
+    if (p == P - 1) col[(W - 1) * STRIDE + SKEW] = c[W - 1];
   }
 
   // 3. plane-by-plane stores of the finished tile; NT: non-temporal stores

@@ -547,3 +547,61 @@ def test_2d_256x256_v65_full_size_sampled_sites():
     say("  worst site rel L2", worst)
     assert worst <= FP32_REL_L2
     lat.close()
+
+
+@pytest.mark.parametrize("nx,nv,dtype,s,nsub,hold,nsteps,scheme", [
+    (1, 3, "f32", 1, 1, 0, 5, "koren"),       # sites repeat in the region
+    (31, 5, "f64", 1, 1, 1, 17, "koren"),
+    (33, 7, "f32", 3, 1, 2, 19, "upwind"),
+    (64, 9, "f64", 1, 2, 3, 40, "koren"),
+    (200, 13, "f32", 2, 1, 1, 11, "koren"),
+    (97, 17, "f64", 1, 1, 1, 9, "upwind"),
+    (257, 17, "f32", 4, 3, 0, 7, "koren"),    # two steps per launch
+    (256, 17, "f32", 8, 1, 0, 4, "koren"),    # the halo leaves no room
+    (1000, 21, "f32", 1, 1, 4, 13, "koren"),
+    (130, 25, "f64", 1, 5, 1, 6, "koren"),
+    (256, 33, "f64", 1, 1, 1, 23, "koren"),
+    (256, 33, "f32", 2, 1, 0, 6, "upwind"),
+    (8192, 33, "f32", 1, 1, 1, 5, "koren"),   # 32-site tiles up to here
+    (8193, 33, "f32", 1, 1, 1, 5, "koren"),   # 64-site tiles from here
+    (8257, 17, "f64", 1, 2, 2, 9, "koren"),
+    (16385, 9, "f64", 1, 1, 1, 6, "koren")])
+def test_1d_several_steps_per_launch(nx, nv, dtype, s, nsub, hold, nsteps,
+                                     scheme):
+    """Short lattices take several steps per launch: a call of nsteps steps
+    against the oracle, against calls of one step (the same bits where the
+    one-step pass is the split-column one, nv 17 and 33), and a call whose
+    flow breaks the CFL bound in its last slice leaves f alone."""
+    import torch
+    from helpers import spec_for
+    from paper_1508_02899_amd import Lattice, LatticeError
+    slices = -(-nsteps // hold) if hold else 1
+    f0, u, p = make_case(1, nx, nv, dtype=dtype, seed=nx + nv, slices=slices,
+                         s=s, nsub=nsub, scheme=scheme)
+    spec = spec_for(f0, p, dtype, hold)
+    ud = torch.from_numpy(u).cuda()
+    args = (p["tau_p"], p["kappa"], p["dt"])
+    with Lattice(spec) as lat:
+        fa = torch.from_numpy(f0).cuda()
+        lat.step(fa, ud, *args, nsteps)
+        lat.sync()
+        fb = torch.from_numpy(f0).cuda()
+        for n in range(nsteps):
+            k = n // hold if hold else 0
+            lat.step(fb, ud[k:k + 1].contiguous(), *args, 1)
+        lat.sync()
+        fc = torch.from_numpy(f0).cuda()
+        bad = ud.clone()
+        bad[-1, 0, nx // 2] = float("nan")
+        lat.step(fc, bad, *args, nsteps)
+        with pytest.raises(LatticeError):
+            lat.sync()
+        assert torch.equal(fc, torch.from_numpy(f0).cuda())
+    bound = FP32_REL_L2 if dtype == "f32" else FP64_REL_L2
+    err = rel_l2(fa.cpu().numpy(), run_oracle(f0, u, p, nsteps, u_hold=hold))
+    say(f"  rel L2 {err:.2e}")
+    assert err <= bound
+    if nv in (17, 33):
+        assert torch.equal(fa, fb)
+    else:
+        assert rel_l2(fa.cpu().numpy(), fb.cpu().numpy()) <= bound
