@@ -557,9 +557,8 @@ __global__ __launch_bounds__(64 * WGW) void k_step2d(
         ystep, yoff0, alpha_scale, beta, D, xg, w, y);
 }
 
-template <typename T, int NV, int P>
-hipError_t launch_step2d_nv(const StepArgs& a, hipStream_t s) {
-  constexpr int WGW = step2d_wgw<T, NV, P>();
+template <typename T, int NV, int P, int WGW, bool BIG>
+hipError_t launch_step2d_shape(const StepArgs& a, hipStream_t s) {
   constexpr int G = OutStage<T, NV, P, WGW>::G;
   if (!step2d_offsets_fit(NV, a.pitch, sizeof(T)) || a.pitch < a.nx * a.ny)
     return hipErrorNotSupported;
@@ -584,18 +583,61 @@ hipError_t launch_step2d_nv(const StepArgs& a, hipStream_t s) {
                        ny, a.pitch, a.shift, xstep, xoff0, ystep, yoff0, as,
                        be, D, ngx, nblocks);
   };
-  if (a.koren) {
-    if (nt)
-      go(k_step2d<T, NV, P, true, true>);
+  if (BIG && nt) {
+    if (a.koren)
+      go(k_step2d<T, NV, P, true, BIG, WGW>);
     else
-      go(k_step2d<T, NV, P, true, false>);
+      go(k_step2d<T, NV, P, false, BIG, WGW>);
   } else {
-    if (nt)
-      go(k_step2d<T, NV, P, false, true>);
+    if (a.koren)
+      go(k_step2d<T, NV, P, true, false, WGW>);
     else
-      go(k_step2d<T, NV, P, false, false>);
+      go(k_step2d<T, NV, P, false, false, WGW>);
   }
   return hipGetLastError();
+}
+
+// Wavefronts of a pass in parts P with one wavefront per workgroup.
+inline int64_t step2d_waves(const StepArgs& a, int P) {
+  const int64_t S = 64 / P;
+  return (a.nx + S - 1) / S * a.ny;
+}
+
+// Small lattices, whose wavefronts all run at once: a pass then takes as long
+// as one wavefront's chain of rows, each row a chain over the W cells of a
+// lane with little to overlap it (deeper row prefetch changes nothing).  So
+// a site's row goes to twice or four times as many lanes while the
+// wavefronts stay few, and every wavefront is a workgroup of its own: no
+// barrier, and no compute unit left with two workgroups while others have
+// one.  The state is below 100 MB: above, short runs of sites per store cost
+// bandwidth.  Measured (Koren, us per step, default shape -> this):
+//   4 P (to 1100 wavefronts): 64 x 48 x 33^2 42.3 -> 21.4, 100 x 90 x 9^2
+//       10.5 -> 8.3; at 2250, 100 x 90 x 33^2: 29.2, with 2 P 26.4
+//   2 P (to 2600): 210 x 150 x 17^2 25.2 -> 19.6, 100 x 90 x 33^2 44.6 ->
+//       26.4, 150 x 130 x 17^2 FP64 30.5 -> 25.9; at 3200, 256 x 200 x 17^2
+//       upwind 21.2 -> 22.9
+//   P (to 2400): 150 x 130 x 33^2 78.7 -> 38.4, 150 x 130 x 21^2 40.4 -> 20.6,
+//       192 x 192 x 17^2 FP64 (2304) 44.4 -> 41.0; at 2560, 300 x 256 x 17^2
+//       upwind 31.5 -> 33.6
+template <typename T, int NV, int P>
+hipError_t launch_step2d_nv(const StepArgs& a, hipStream_t s) {
+  const bool small = (uint64_t)NV * NV * (uint64_t)a.pitch * sizeof(T) <=
+                     100000000ull;
+  if constexpr (NV >= 7 && NV < 65 && (NV - 1) % (4 * P) == 0 &&
+                (NV - 1) / (4 * P) >= 2 && sizeof(T) == 4) {
+    if (small && step2d_waves(a, 4 * P) <= 1100)
+      return launch_step2d_shape<T, NV, 4 * P, 1, false>(a, s);
+  }
+  if constexpr (NV >= 7 && (NV - 1) % (2 * P) == 0 &&
+                (NV - 1) / (2 * P) >= 2) {
+    if (small && step2d_waves(a, 2 * P) <= 2600)
+      return launch_step2d_shape<T, NV, 2 * P, 1, false>(a, s);
+  }
+  if constexpr (NV >= 7) {
+    if (small && step2d_waves(a, P) <= 2400)
+      return launch_step2d_shape<T, NV, P, 1, false>(a, s);
+  }
+  return launch_step2d_shape<T, NV, P, step2d_wgw<T, NV, P>(), true>(a, s);
 }
 
 }  // namespace lat

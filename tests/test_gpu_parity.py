@@ -605,3 +605,42 @@ def test_1d_several_steps_per_launch(nx, nv, dtype, s, nsub, hold, nsteps,
         assert torch.equal(fa, fb)
     else:
         assert rel_l2(fa.cpu().numpy(), fb.cpu().numpy()) <= bound
+
+
+@pytest.mark.parametrize("nv,dtype,nx,ny,scheme", [
+    (7, "f32", 33, 7, "koren"), (9, "f32", 70, 5, "upwind"),
+    (9, "f32", 1101, 16, "koren"), (11, "f32", 65, 3, "koren"),
+    (13, "f32", 17, 9, "koren"), (15, "f32", 40, 6, "upwind"),
+    (17, "f32", 9, 8, "koren"), (17, "f32", 137, 67, "koren"),
+    (17, "f32", 137, 270, "koren"), (19, "f32", 33, 5, "koren"),
+    (21, "f32", 50, 4, "upwind"), (25, "f32", 13, 5, "koren"),
+    (33, "f32", 5, 3, "koren"), (33, "f32", 67, 70, "upwind"),
+    (33, "f32", 132, 67, "koren"), (65, "f32", 7, 5, "koren"),
+    (9, "f64", 35, 6, "koren"), (17, "f64", 21, 5, "koren"),
+    (33, "f64", 6, 5, "koren"), (33, "f64", 40, 66, "koren")])
+def test_2d_small_lattice_shapes(nv, dtype, nx, ny, scheme):
+    """Every shape of the small-lattice pass (4, 2 and 1 times the parts, one
+    wavefront per workgroup) with ragged tiles: against the oracle, and the
+    same bits as the pass of a lattice too large for it (the same sites
+    repeated along y, which the update does not notice)."""
+    import torch
+    from paper_1508_02899_amd import Lattice
+    from helpers import spec_for
+    f0, u, p = make_case(2, nx, nv, ny=ny, dtype=dtype, seed=nx * ny + nv,
+                         scheme=scheme)
+    bound = FP32_REL_L2 if dtype == "f32" else FP64_REL_L2
+    got = run_gpu(f0, u, p, 2, dtype)
+    err = rel_l2(got, run_oracle(f0, u, p, 2))
+    say(f"  rel L2 {err:.2e}")
+    assert err <= bound
+    reps = 2600 * 64 // (nx * ny) + 1  # past 2600 wavefronts at any shape
+    if reps * f0.nbytes <= 2 << 30:
+        fb = np.tile(f0, (1, reps, 1))
+        ub = np.tile(u, (1, 1, reps, 1))
+        q = dict(p)
+        with Lattice(spec_for(fb, q, dtype)) as lat:
+            fd = torch.from_numpy(fb).cuda()
+            lat.step(fd, torch.from_numpy(ub).cuda(), p["tau_p"], p["kappa"],
+                     p["dt"], 2)
+            lat.sync()
+            assert np.array_equal(fd[:, :ny].cpu().numpy(), got)
