@@ -290,8 +290,10 @@ int lattice_s1(lattice_t* L, const void* f, double dt, int32_t nr,
  *   ky + kmax), kx = 0..kmax; psi(ix, iy) = sum Re(c e^{2 pi i (kx ix/nx +
  *   ky iy/ny)}), u[s][0] = d psi/dy, u[s][1] = -d psi/dx with the site
  *   spacing dx of the lattice (domain nx dx by ny dx).  Two separable passes
- *   (along x, then along y) through a stream-ordered temporary of
- *   2 (2 kmax + 1) nx n_slices complex values.  1 <= kmax <= 64,
+ *   (along x, then along y) through a workspace of 4 (kmax + 1) nx reals
+ *   per slice, of which the handle keeps up to 32 MB (or one slice's) from
+ *   the first call on; more slices go through it in turn.  A call under
+ *   stream capture uses a stream-ordered temporary instead.  1 <= kmax <= 64,
  *   2 kmax < nx, ny; n_slices, ny <= 65535.  EINVAL, EHIP.
  */
 int lattice_flow1d_modes(lattice_t* L, int32_t nmodes, const float* coef,

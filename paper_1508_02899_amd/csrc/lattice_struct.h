@@ -29,6 +29,8 @@ struct lattice {
   double* s1_work = nullptr;
   size_t s1_bytes = 0;
   void* s1_blas = nullptr;
+  void* flow_work = nullptr;  // lattice_flow2d_modes, from its first call on
+  size_t flow_bytes = 0;
   char msg[512];
   // profiling
   bool prof = false;

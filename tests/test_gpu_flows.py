@@ -48,6 +48,65 @@ def test_flow2d_modes_match_oracle(dtype, nx, ny, K, ns):
     lat.close()
 
 
+@pytest.mark.parametrize("dtype,nx,ny,K,ns", [
+    ("f32", 3, 3, 1, 1), ("f32", 131, 133, 64, 2), ("f64", 129, 131, 64, 1),
+    ("f32", 65, 33, 15, 5), ("f64", 63, 31, 14, 3),
+    ("f32", 2048, 130, 64, 17)])  # two chunks of slices
+def test_flow2d_edges_and_chunks(dtype, nx, ny, K, ns):
+    """Ragged tiles of sites and rows, the smallest and largest tables, more
+    slices than the workspace holds at once, then a smaller call.  FP32: each
+    of 2 K + 1 terms of a sum carries a few roundings of 2^-24, as in the
+    test above."""
+    import torch
+    from oracle import flows as F
+    from paper_1508_02899_amd import Lattice, LatticeSpec
+    rng = np.random.default_rng(24 + nx)
+    tab = rng.standard_normal((ns, 2 * K + 1, K + 1, 2)).astype(np.float32)
+    lat = Lattice(LatticeSpec(dim=2, nx=nx, ny=ny, nv=3, dx=0.05,
+                              dtype=dtype))
+    td = torch.from_numpy(tab).cuda()
+    u = lat.flow_from_modes(td).cpu().numpy()
+    bound = 5e-6 if dtype == "f32" else 1e-12
+    for s in sorted({0, ns // 2, ns - 1}):
+        err = rel_l2(u[s], F.flow2d(tab[s:s + 1], nx, ny, 0.05)[0])
+        assert err < bound, (s, err)
+    v = lat.flow_from_modes(td[-1:].contiguous()).cpu().numpy()
+    assert np.array_equal(u[-1:], v)
+    lat.close()
+
+
+def test_flow2d_under_capture():
+    """A captured call replays on new tables after the handle's own
+    workspace has grown."""
+    import torch
+    from paper_1508_02899_amd import Lattice, LatticeSpec
+    st = torch.cuda.Stream()
+    spec = LatticeSpec(dim=2, nx=64, ny=48, nv=3, dx=0.05)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    tabs = [torch.randn((2, 17, 9, 2), generator=g, device="cuda")
+            for _ in range(3)]
+    coef = tabs[0].clone()
+    out = torch.empty((2, 2, 48, 64), device="cuda")
+    lat = Lattice(spec, stream=st)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        lat.flow_from_modes(coef, out=out)
+    big = torch.randn((9, 41, 21, 2), generator=g, device="cuda")
+    for t in tabs:
+        coef.copy_(t)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = out.clone()
+        lat.flow_from_modes(big)
+        want = lat.flow_from_modes(t)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+    lat.close()
+
+
 def test_steps_with_device_flow_match_prestaged_flow():
     """2D Koren steps driven by flows synthesised on the device equal the
     steps driven by the prestaged inverse-FFT flows up to the FP32 rounding
