@@ -289,12 +289,6 @@ static int run_call(const lattice_desc& d, CallPlan& p, void* f,
     }
     return true;
   };
-  if (p.used > 0 &&
-      !chk(lat::launch_cfl_check(u, p.used * p.slice_len, p.umax_ok,
-                                 d.scheme == LATTICE_UPWIND ? 1 : 0,
-                                 d.dtype == LATTICE_F64, flag, st),
-           "cfl check launch"))
-    return LATTICE_EHIP;
   // Short 1D lattices: several steps per launch, spread evenly over an even
   // number of launches (no copy needed) unless there is only one step;
   // profiled runs time every step by itself.
@@ -307,15 +301,23 @@ static int run_call(const lattice_desc& d, CallPlan& p, void* f,
       launches += launches & 1;
     }
   }
-  void* bufs[2];
-  if (launches % 2 == 0) {
-    bufs[0] = f;
-    bufs[1] = twin;
-  } else {
-    if (!chk(lat::launch_copy(twin, f, state_bytes, st), "state copy"))
-      return LATTICE_EHIP;
+  void* bufs[2] = {f, twin};
+  int64_t copy = 0;  // bytes of f that start in the twin
+  if (launches % 2 != 0) {
     bufs[0] = twin;
     bufs[1] = f;
+    copy = state_bytes;
+  }
+  if (p.used > 0) {
+    if (!chk(lat::launch_check_copy(u, p.used * p.slice_len, p.umax_ok,
+                                    d.scheme == LATTICE_UPWIND ? 1 : 0,
+                                    d.dtype == LATTICE_F64, flag, twin, f,
+                                    copy, st),
+             "cfl check launch"))
+      return LATTICE_EHIP;
+  } else if (copy > 0 && !chk(lat::launch_copy(twin, f, copy, st),
+                              "state copy")) {
+    return LATTICE_EHIP;
   }
   lat::StepArgs& a = p.a;
   a.flag = flag;

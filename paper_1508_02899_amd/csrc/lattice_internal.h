@@ -52,9 +52,11 @@ hipError_t launch_step1d_multi(const StepArgs& a, int nsteps, int64_t step0,
 hipError_t launch_step2d(const StepArgs& a, hipStream_t s);
 
 // Sticky CFL / finiteness check of the u slices: sets flag |= 1 when some
-// |u| exceeds umax_ok (strict: |u| >= umax_ok) or is not finite.
-hipError_t launch_cfl_check(const void* u, int64_t n, double umax_ok,
-                            int strict, int f64, int* flag, hipStream_t s);
+// |u| exceeds umax_ok (strict: |u| >= umax_ok) or is not finite; and
+// dst[0..bytes) = src (bytes may be 0), in the same launch where it can be.
+hipError_t launch_check_copy(const void* u, int64_t n, double umax_ok,
+                             int strict, int f64, int* flag, void* dst,
+                             const void* src, int64_t bytes, hipStream_t s);
 // max |u| over n values into *out (FP64 on device, reset inside).
 hipError_t launch_absmax(const void* u, int64_t n, int f64, double* out,
                          hipStream_t s);
