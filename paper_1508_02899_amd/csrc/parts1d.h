@@ -290,21 +290,25 @@ struct Parts1DTile {
 
 // The whole update of one tile: load, put, barrier, collide, barrier,
 // store.  A caller that reuses the tile synchronises again before the
-// next put.
+// next put.  A short lattice's pass is a chain of latencies, so the flag and
+// the flow value travel together with the tile's loads, and the flag is
+// looked at before the stores only (16384 x 129: 5.6 -> 5.3 us a step).
 template <typename T, int NV, int P, int WGW, bool KOREN>
 __device__ __forceinline__ void parts1d_tile(
     const T* __restrict__ fin, T* __restrict__ fout, const T* __restrict__ u,
-    T* __restrict__ tile, int nx, int pitch, int x0, int step_mod,
-    int init_off, int jump, int nsub, T alpha_scale, T beta, T D) {
+    const int* __restrict__ flag, T* __restrict__ tile, int nx, int pitch,
+    int x0, int step_mod, int init_off, int jump, int nsub, T alpha_scale,
+    T beta, T D) {
   using PT = Parts1DTile<T, NV, P, WGW>;
   T r[PT::K];
+  const int stop = *flag;
   PT::load(fin, nx, pitch, x0, step_mod, init_off, jump, r);
+  const T alpha = PT::alpha_at(u, nx, x0, alpha_scale);
   PT::put(tile, r);
   __syncthreads();
-  const T alpha = PT::alpha_at(u, nx, x0, alpha_scale);
   PT::template collide<KOREN>(tile, alpha, nsub, beta, D);
   __syncthreads();
-  PT::store(tile, fout, nx, pitch, x0);
+  if (stop == 0) PT::store(tile, fout, nx, pitch, x0);  // uniform
 }
 
 }  // namespace lat
