@@ -284,9 +284,9 @@ template <typename T, int NV, int P, bool KOREN, bool INTERIOR, int WGW,
           bool NT>
 __device__ __forceinline__ void step2d_tile(
     const T* __restrict__ fin, T* __restrict__ fout, const T* __restrict__ u,
-    T* __restrict__ stage, int nx, int ny, size_t pitch, int shift, int xstep,
-    int xoff0, int ystep, int yoff0, T alpha_scale, T beta, T D, int xg, int w,
-    int y) {
+    const int* __restrict__ flag, T* __restrict__ stage, int nx, int ny,
+    size_t pitch, int shift, int xstep, int xoff0, int ystep, int yoff0,
+    T alpha_scale, T beta, T D, int xg, int w, int y) {
   using K = Step2D<T, NV, P, KOREN>;
   using O = OutStage<T, NV, P, WGW>;
   constexpr int W = K::W, S = K::S, H = K::H, G = O::G;
@@ -449,10 +449,14 @@ __device__ __forceinline__ void step2d_tile(
   // first g- is zero on every lane, then neither half, then g+), so that
   // each loop keeps its state in the same registers from trip to trip.
   T bufA[W], bufB[W];
+  const int stop = *flag;
   load_row(0, ys, bufA);
   ys = next_ys(ys);
   load_row(1, ys, bufB);
   ys = next_ys(ys);
+  // the flag travels with the first rows; the loads stay before the branch
+  asm volatile("" ::: "memory");
+  if (stop != 0) return;  // uniform over the grid
   run_row(edge_t(), 0, bufA, st);
   load_row(2, ys, bufA);
   ys = next_ys(ys);
@@ -533,7 +537,6 @@ __global__ __launch_bounds__(64 * WGW) void k_step2d(
   constexpr int S = 64 / P;
   constexpr int H = (NV - 1) / 2;
   __shared__ T stage[P > 1 ? 2 * O::SIZE : 1];
-  if (*flag != 0) return;  // uniform over the grid
   // whole rows of tiles per XCD, rows interleaved over the XCDs: the tiles
   // of a row, which read the same cache lines at their edges, meet in one
   // L2, and the rows in flight are consecutive (measured on 512^2 x 33^2:
@@ -549,11 +552,11 @@ __global__ __launch_bounds__(64 * WGW) void k_step2d(
                         x0 + S - 1 + shift * H <= nx - 1;
   if (interior)
     step2d_tile<T, NV, P, KOREN, true, WGW, NT>(
-        fin, fout, u, stage, nx, ny, (size_t)pitch, shift, xstep, xoff0,
+        fin, fout, u, flag, stage, nx, ny, (size_t)pitch, shift, xstep, xoff0,
         ystep, yoff0, alpha_scale, beta, D, xg, w, y);
   else
     step2d_tile<T, NV, P, KOREN, false, WGW, NT>(
-        fin, fout, u, stage, nx, ny, (size_t)pitch, shift, xstep, xoff0,
+        fin, fout, u, flag, stage, nx, ny, (size_t)pitch, shift, xstep, xoff0,
         ystep, yoff0, alpha_scale, beta, D, xg, w, y);
 }
 
