@@ -858,23 +858,24 @@ __global__ __launch_bounds__(256) void k_mlp_grad_mfma(
 // Sum of the partial rows, fixed order: a block takes 64 consecutive
 // entries (coalesced row reads); its 16 wavefronts sum rows q, q+16, ...
 // (q = wavefront), 16 rows' loads in flight, and the sums are added pairwise.
-// With bc1 > 0 the Adam update (Kingma & Ba 2015) of those parameters
-// follows at once; bc1 = 1 - b1^t and bc2 = 1 - b2^t come from the host in
-// double, where 1 - b2^t does not cancel.  A latency chain (load, tree,
-// update): 256 rows 3.4 us, with eight wavefronts, the moments loaded after
-// the sum and powf 6.35 us.
+// With adam_step > 0 the Adam update (Kingma & Ba 2015) of those parameters
+// follows at once.  A latency chain (load, tree, update): 256 rows 3.7 us;
+// 6.35 us with eight wavefronts, and the moments and the powers after the
+// sum instead of beside its loads.
 constexpr int kRedWaves = 16;
 __global__ __launch_bounds__(64 * kRedWaves) void k_grad_reduce(
     const float* __restrict__ partial, int nrows, float* __restrict__ grad,
     float* __restrict__ loss, float* __restrict__ P, float* __restrict__ m,
-    float* __restrict__ v, float bc1, float bc2, float lr, float b1, float b2,
+    float* __restrict__ v, int adam_step, float lr, float b1, float b2,
     float eps) {
   __shared__ float sh[kRedWaves][64];
   const int q = (int)threadIdx.x >> 6, j = (int)threadIdx.x & 63;
   const int p = (int)blockIdx.x * 64 + j;
-  const bool adam = bc1 > 0.f && q == 0 && p < kNParams;
-  float m0 = 0.f, v0 = 0.f, p0 = 0.f;
+  const bool adam = adam_step > 0 && q == 0 && p < kNParams;
+  float m0 = 0.f, v0 = 0.f, p0 = 0.f, bc1 = 0.f, bc2 = 0.f;
   if (adam) {
+    bc1 = 1.f - powf(b1, (float)adam_step);
+    bc2 = 1.f - powf(b2, (float)adam_step);
     m0 = m[p];
     v0 = v[p];
     p0 = P[p];
@@ -1262,8 +1263,7 @@ hipError_t launch_grad_reduce(const float* partial, int nrows, float* grad,
   hipLaunchKernelGGL(k_grad_reduce, dim3((kNParams + 1 + 63) / 64),
                      dim3(64 * kRedWaves), 0, s, partial, nrows, grad, loss,
                      (float*)nullptr,
-                     (float*)nullptr, (float*)nullptr, 0.f, 0.f, 0.f, 0.f, 0.f,
-                     0.f);
+                     (float*)nullptr, (float*)nullptr, 0, 0.f, 0.f, 0.f, 0.f);
   return hipGetLastError();
 }
 
@@ -1274,8 +1274,7 @@ hipError_t launch_grad_reduce_adam(const float* partial, int nrows,
                                    hipStream_t s) {
   hipLaunchKernelGGL(k_grad_reduce, dim3((kNParams + 1 + 63) / 64),
                      dim3(64 * kRedWaves), 0, s, partial, nrows, grad, loss,
-                     params, m, v, (float)(1.0 - pow((double)b1, step)),
-                     (float)(1.0 - pow((double)b2, step)), lr, b1, b2, eps);
+                     params, m, v, step, lr, b1, b2, eps);
   return hipGetLastError();
 }
 
