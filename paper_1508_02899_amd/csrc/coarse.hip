@@ -115,6 +115,8 @@ struct MlpRegs {
   float b3;
 };
 
+// ALL: w3 in every row of a3 (else in row 0 only).
+template <bool ALL = false>
 __device__ void load_mlp(MlpRegs& R, const float* __restrict__ P,
                          const uint16_t* __restrict__ wq) {
   const int l = (int)threadIdx.x & 63;
@@ -143,7 +145,7 @@ __device__ void load_mlp(MlpRegs& R, const float* __restrict__ P,
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       R.a3[kk][i] =
-          col == 0 ? (short)wq[kOffW3 + kunit(kk, ks, i)] : (short)0;
+          ALL || col == 0 ? (short)wq[kOffW3 + kunit(kk, ks, i)] : (short)0;
   R.b3 = P[kOffB3];
 }
 
@@ -176,11 +178,16 @@ __device__ __forceinline__ float mlp_forward(const MlpRegs& R, bf16x4 x) {
 
 // The same network with the layer biases read from LDS (b1s, b2s: the 64
 // biases of each hidden layer, 16-byte aligned): a kernel that keeps the
-// weights in registers for its whole run frees the 32 bias registers.
+// weights in registers for its whole run frees the 32 bias registers.  w3
+// (R.a3 in every row, load_mlp<true>) enters as row 4q of the last operand
+// (q: uniform), so that the outputs of the 16 columns come back in lanes 16q
+// .. 16q + 15.
 __device__ __forceinline__ float mlp_forward_lds(const MlpRegs& R,
                                                  const float* b1s,
-                                                 const float* b2s, bf16x4 x) {
-  const int ks = ((int)threadIdx.x & 63) >> 4;
+                                                 const float* b2s, bf16x4 x,
+                                                 int q) {
+  const int l = (int)threadIdx.x & 63;
+  const int ks = l >> 4;
   bf16x4 h1[4], h2[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -196,10 +203,17 @@ __device__ __forceinline__ float mlp_forward_lds(const MlpRegs& R,
       d = mfma32(R.a2[u][kk], cat8(h1[2 * kk], h1[2 * kk + 1]), d);
     h2[u] = pack4(gelu(d[0]), gelu(d[1]), gelu(d[2]), gelu(d[3]));
   }
+  const bool row = (l & 15) == 4 * q;
   f32x4 y = {R.b3, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int kk = 0; kk < 2; ++kk)
-    y = mfma32(R.a3[kk], cat8(h2[2 * kk], h2[2 * kk + 1]), y);
+  for (int kk = 0; kk < 2; ++kk) {
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 a = __builtin_bit_cast(u32x4, R.a3[kk]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = row ? a[i] : 0u;
+    y = mfma32(__builtin_bit_cast(s16x8, a), cat8(h2[2 * kk], h2[2 * kk + 1]),
+               y);
+  }
   return y[0];
 }
 
@@ -1066,23 +1080,15 @@ void k_mlp_correct17(
   if (tid < 2 * kNH)
     bsh[tid / kNH][tid % kNH] = P[(tid < kNH ? kOffB1 : kOffB2) + tid % kNH];
   MlpRegs R;
-  load_mlp(R, P, wq);
+  load_mlp<true>(R, P, wq);
   __syncthreads();
   const int col = l & 15, ks = l >> 4;
   for (int s = w; s < nts; s += 4) {
     const float ux = us[0][s], uy = us[1][s];
-    // a face's line as a base and a stride into the tile, so that x- and
-    // y-faces in one pass of 16 take the same instructions
-    // (24-bit index products: full-rate multiplies)
+    // (a face's line is a base and a stride into the tile, so that x- and
+    // y-faces of one pass take the same instructions; 24-bit index products:
+    // full-rate multiplies)
     const float* const tcol = &tile[0][s];
-    auto feat = [&](int fid, float* st, float* ms, float* sg, float* anu) {
-      int axis, a, k;
-      face_of(fid, &axis, &a, &k);
-      const int boff = __umul24(axis == 0 ? a * NV : a, kTS + 1);
-      const int soff = axis == 0 ? kTS + 1 : NV * (kTS + 1);
-      auto ln = [&](int c) { return tcol[boff + __umul24(c, soff)]; };
-      face_feat(ln, NV, k, axis == 0 ? ux : uy, g, st, ms, sg, anu);
-    };
     // the faces that get a correction: lanes 0..NV-1 take the rows (x-faces),
     // lanes 32..32+NV-1 the columns (y-faces) of the site; each keeps the
     // prefix sums of its line in registers (Pf[c] = sum of the cells < c)
@@ -1131,28 +1137,45 @@ void k_mlp_correct17(
     }
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    for (int c0 = 0; c0 < nq; c0 += 16) {
-      const int e = c0 + col;
-      const bool live = e < nq;
-      const int fid = live ? (int)queue[w][e] : 0;
+    // 64 faces at a time, one per lane, for their features and fluxes; the
+    // network takes them 16 at a time, lane (col, ks) its share of the
+    // features of face 16 q + col by lane exchange
+    for (int c0 = 0; c0 < nq; c0 += 64) {
+      const bool live = c0 + l < nq;
+      const int fid = live ? (int)queue[w][c0 + l] : 0;
+      int axis, a, k;
+      face_of(fid, &axis, &a, &k);
+      const int boff = __umul24(axis == 0 ? a * NV : a, kTS + 1);
+      const int soff = axis == 0 ? kTS + 1 : NV * (kTS + 1);
       float st[5], ms, sg, anu;
-      feat(fid, st, &ms, &sg, &anu);
+      {
+        auto ln = [&](int c) { return tcol[boff + __umul24(c, soff)]; };
+        face_feat(ln, NV, k, axis == 0 ? ux : uy, g, st, &ms, &sg, &anu);
+      }
       // 1/m_s to 1 ulp (the features are rounded to bf16 next)
-      const float inv = ms > 0.f ? __builtin_amdgcn_rcpf(ms) : 0.f;
-      bf16x4 x;
-      if (ks == 0 && live)
-        x = pack4(st[0] * inv, st[1] * inv, st[2] * inv, st[3] * inv);
-      else if (ks == 1 && live)
-        x = pack4(st[4] * inv, anu, g.log_st, 0.f);
-      else
-        x = pack4(0.f, 0.f, 0.f, 0.f);
-      const float y = mlp_forward_lds(R, bsh[0], bsh[1], x);
-      if (l < 16 && live) {
-        int axis, a, k;
-        face_of(fid, &axis, &a, &k);
+      const float inv = live && ms > 0.f ? __builtin_amdgcn_rcpf(ms) : 0.f;
+      const u32x2 lo = __builtin_bit_cast(
+          u32x2, pack4(st[0] * inv, st[1] * inv, st[2] * inv, st[3] * inv));
+      const u32x2 hi = __builtin_bit_cast(
+          u32x2, pack4(st[4] * inv, anu, g.log_st, 0.f));
+      float y = 0.f;
+#pragma unroll 1
+      for (int q = 0; q < 4 && c0 + 16 * q < nq; ++q) {
+        const int src = (16 * q + col) << 2;
+        u32x2 x;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int xl = __builtin_amdgcn_ds_bpermute(src, (int)lo[i]);
+          const int xh = __builtin_amdgcn_ds_bpermute(src, (int)hi[i]);
+          // K = 4 ks + i: features 0..3, 4..7, and two groups of zeros
+          x[i] = ks == 0 ? (unsigned)xl : (ks == 1 ? (unsigned)xh : 0u);
+        }
+        const float yq = mlp_forward_lds(R, bsh[0], bsh[1],
+                                         __builtin_bit_cast(bf16x4, x), q);
+        y = ks == q ? yq : y;
+      }
+      if (live) {
         float G = sg * ms * y;
-        const int boff = __umul24(axis == 0 ? a * NV : a, kTS + 1);
-        const int soff = axis == 0 ? kTS + 1 : NV * (kTS + 1);
         const float donor = tcol[boff + __umul24(G > 0.f ? k - 1 : k, soff)];
         const float cap = 0.25f * donor;
         G = G > cap ? cap : (G < -cap ? -cap : G);
