@@ -207,6 +207,7 @@ struct CallPlan {
   int64_t slice_len = 0;   // elements of one u slice
   int64_t used = 0;        // u slices the device check reads
   double umax_ok = 0.0;    // |u| bound of Eq. 3 for this call
+  lat::lattice_dims dims = {};  // 2D
   int64_t passes_per_step = 1;
   int64_t passes = 0;
 };
@@ -254,8 +255,15 @@ static int plan_call(const lattice_desc& d, int64_t sites, size_t elem,
   p->slice_len = (int64_t)d.dim * sites;
   p->used = drag ? need : 0;
   // per step, 1D does everything in one pass (nsub inline); 2D does one
-  // streaming pass plus (nsub - 1) collision-only passes.
-  p->passes_per_step = d.dim == 1 ? 1 : d.nsub;
+  // streaming pass and further collision-only passes, each with as many of
+  // the sub-steps as step2d_sub_take gives it.
+  if (d.dim == 2) {
+    p->dims = {d.nv, d.dtype == LATTICE_F64, d.scheme == LATTICE_KOREN, d.nx,
+               d.ny, plane_pitch_of(d)};
+    p->passes_per_step = 0;
+    for (int64_t left = d.nsub; left > 0; ++p->passes_per_step)
+      left -= lat::step2d_sub_take(p->dims, left);
+  }
   p->passes = nsteps * p->passes_per_step;
   lat::StepArgs& a = p->a;
   a.nx = d.nx;
@@ -339,13 +347,19 @@ static int run_call(const lattice_desc& d, CallPlan& p, void* f,
   for (int64_t s = 0; s < nsteps; ++s) {
     const int64_t sl = d.u_hold > 0 ? s / d.u_hold : 0;
     a.u = (const char*)u + (size_t)(sl * p.slice_len) * elem;
+    int64_t left = d.nsub;
     for (int64_t ps = 0; ps < p.passes_per_step; ++ps, ++k) {
       a.fin = bufs[k & 1];
       a.fout = bufs[(k + 1) & 1];
       a.shift = (ps == 0 && stream) ? d.vstride : 0;
+      if (d.dim == 2) {  // this pass's share of the sub-steps
+        a.nsub_inline = lat::step2d_sub_take(p.dims, left);
+        left -= a.nsub_inline;
+      }
       if (L && !chk(record_pair(L, false), "event record")) return LATTICE_EHIP;
-      hipError_t e = d.dim == 1 ? lat::launch_step1d(a, st)
-                                : lat::launch_step2d(a, st);
+      hipError_t e = d.dim == 1           ? lat::launch_step1d(a, st)
+                     : a.nsub_inline > 1 ? lat::launch_step2d_sub(a, st)
+                                         : lat::launch_step2d(a, st);
       if (!chk(e, "step kernel launch")) return LATTICE_EHIP;
       if (L && !chk(record_pair(L, true), "event record")) return LATTICE_EHIP;
     }

@@ -19,7 +19,7 @@ struct StepArgs {
   int64_t pitch;     // elements between velocity planes of fin / fout
   int nv;
   int shift;         // cells moved per velocity index (vstride or 0)
-  int nsub_inline;   // 1D only: collision sub-steps done inside the pass
+  int nsub_inline;   // collision sub-steps done inside the pass
   double alpha_scale;  // dt_s / (dv tau_p): drift of cell j in cell widths
   double beta;         // dt_s / tau_p       is alpha_scale*u - beta*(j-h)
   double D;            // kappa dt_s / dv^2
@@ -50,6 +50,16 @@ int step1d_multi_steps(int nv, int64_t nx, int shift, int nsub, int f64);
 hipError_t launch_step1d_multi(const StepArgs& a, int nsteps, int64_t step0,
                                int64_t u_hold, hipStream_t s);
 hipError_t launch_step2d(const StepArgs& a, hipStream_t s);
+// One pass with a.nsub_inline >= 2 collision sub-steps; step2d_sub_take: how
+// many of the sub-steps left the next pass takes (1: launch_step2d);
+// step2d_sub_large: past the caches, in the wider shape.
+struct lattice_dims {
+  int nv, f64, koren;
+  int64_t nx, ny, pitch;
+};
+int step2d_sub_take(const lattice_dims& d, int64_t left);
+bool step2d_sub_large(int nv, int64_t pitch, int f64);
+hipError_t launch_step2d_sub(const StepArgs& a, hipStream_t s);
 
 // Sticky CFL / finiteness check of the u slices: sets flag |= 1 when some
 // |u| exceeds umax_ok (strict: |u| >= umax_ok) or is not finite; and

@@ -1,0 +1,86 @@
+// step2d_sub_f64.hip -- FP64 2D passes with several sub-steps, and the rule
+// that says how many a pass takes.
+#include "step2d_sub.h"
+
+namespace lat {
+hipError_t step2d_sub_f32_a(const StepArgs& a, hipStream_t s);
+hipError_t step2d_sub_f32_b(const StepArgs& a, hipStream_t s);
+hipError_t step2d_sub_f32_c(const StepArgs& a, hipStream_t s);
+
+namespace {
+
+// Parts of the small shape (0: no kernel).
+int sub_parts(int nv, int f64) {
+  switch (nv) {
+    case 5: return 2;
+    case 9: return f64 ? 4 : 2;
+    case 13: case 21: return f64 ? 0 : 4;
+    case 17: return f64 ? 8 : 4;
+    case 25: return f64 ? 0 : 8;
+    case 33: return f64 ? 16 : 8;
+    case 65: return f64 ? 0 : 16;
+    default: return 0;
+  }
+}
+
+}  // namespace
+
+bool step2d_sub_large(int nv, int64_t pitch, int f64) {
+  return !f64 && (int64_t)nv * nv * pitch * 4 > (128ll << 20);
+}
+
+// How many of `left` sub-steps the next pass takes.  Measured against a pass
+// per sub-step with the shapes of step2d.h at their start (us per step of 2,
+// 3, 4 sub-steps, Koren unless said):
+//   Small lattices (all wavefronts run at once, a pass is one wavefront's
+//   chain of rows): 64 x 48 x 33^2 84.6, 125.8, 167.1 -> 31.4, 34.3, 37.2;
+//   100 x 90 x 17^2 47.5, 70.1, 92.5 -> 22.4, 26.3, 29.8; 64 x 48 x 17^2 FP64
+//   43.4, 63.8, 84.2 -> 23.3, 27.2, 30.8.  Past 8000 wavefronts (2500 in FP64)
+//   the stages compete for the compute units: 256^2 x 17^2 (8192) 52.8 ->
+//   56.5, 210 x 150 x 17^2 FP64 (12150) 123 -> 170.
+//   Large lattices, bound by memory: FP32 only (FP64 is bound by its
+//   arithmetic).  65^2, 256^2 sites: 834, 1238, 1646 -> 737, 1272, 1359;
+//   33^2, 512^2 sites: 835, 1249, 1665 -> 737, 1474, 1632; upwind 823, 1238,
+//   1649 -> 559, 1008, 1097.  Three stages of two wavefronts leave two of the
+//   four SIMDs with half the work, and four are no better than two twice
+//   under Koren below 65^2.  In one wavefront per stage: 400 x 300 x 17^2
+//   151, 224, 301 -> 101, 157, 227, upwind 136, 204, 274 -> 76, 102, 132;
+//   512^2 x 17^2 232 -> 246 and 512^2 x 21^2 381 -> 416 under Koren, where
+//   the state is past 256 MB.
+int step2d_sub_take(const lattice_dims& d, int64_t left) {
+  const int P = sub_parts(d.nv, d.f64);
+  if (P == 0 || left < 2) return 1;
+  int64_t most;
+  if (step2d_sub_large(d.nv, d.pitch, d.f64)) {
+    const bool past = (int64_t)d.nv * d.nv * d.pitch * 4 > (256ll << 20);
+    most = !d.koren || d.nv >= 65 ? kSubMax
+           : past && (d.nv == 17 || d.nv == 21) ? 1 : 2;
+    if (d.nv >= 25) return left >= 4 && most == 4 ? 4 : 2;
+  } else {
+    const int64_t S = 64 / P;
+    const int64_t waves = (d.nx + S - 1) / S * d.ny;
+    most = (d.f64 ? 2500 : 8000) / waves;
+    if (most > kSubMax) most = kSubMax;
+  }
+  if (most < 2) return 1;
+  const int64_t passes = (left + most - 1) / most;
+  return (int)((left + passes - 1) / passes);
+}
+
+hipError_t launch_step2d_sub(const StepArgs& a, hipStream_t s) {
+  if (sub_parts(a.nv, a.f64) == 0 || a.nx < 1 || a.ny < 1)
+    return hipErrorInvalidValue;
+  if (a.f64) {
+    switch (a.nv) {
+      case 5: return launch_step2d_sub_nv<double, 5, 2, 0>(a, s);
+      case 9: return launch_step2d_sub_nv<double, 9, 4, 0>(a, s);
+      case 17: return launch_step2d_sub_nv<double, 17, 8, 0>(a, s);
+      default: return launch_step2d_sub_nv<double, 33, 16, 0>(a, s);
+    }
+  }
+  if (a.nv <= 21) return step2d_sub_f32_a(a, s);
+  if (a.nv <= 33) return step2d_sub_f32_b(a, s);
+  return step2d_sub_f32_c(a, s);
+}
+
+}  // namespace lat

@@ -644,3 +644,64 @@ def test_2d_small_lattice_shapes(nv, dtype, nx, ny, scheme):
                      p["dt"], 2)
             lat.sync()
             assert np.array_equal(fd[:, :ny].cpu().numpy(), got)
+
+
+@pytest.mark.parametrize("nv,dtype,nx,ny,scheme", [
+    (5, "f32", 70, 9, "koren"), (5, "f64", 33, 4, "upwind"),
+    (9, "f32", 37, 5, "upwind"), (9, "f64", 19, 6, "koren"),
+    (13, "f32", 50, 7, "koren"), (17, "f32", 130, 11, "koren"),
+    (17, "f64", 9, 5, "koren"), (21, "f32", 33, 8, "koren"),
+    (25, "f32", 12, 6, "upwind"), (33, "f32", 17, 9, "koren"),
+    (33, "f64", 6, 5, "koren"), (65, "f32", 6, 5, "koren"),
+    # the shapes of states past 128 MB, and a lattice of one pass per sub-step
+    (65, "f32", 97, 83, "koren"), (33, "f32", 203, 160, "upwind"),
+    (25, "f32", 301, 181, "koren"), (17, "f32", 350, 339, "koren"),
+    (17, "f64", 64, 70, "koren"), (7, "f32", 40, 9, "koren")])
+def test_2d_sub_steps_in_one_pass(nv, dtype, nx, ny, scheme):
+    """2, 3, 4 and 5 collision sub-steps (one to three passes): bit for bit
+    the streaming followed by single collisions with the same coefficients
+    (2 and 4: tau_p and kappa scale by powers of two), the small ones also
+    against the oracle."""
+    import torch
+    from dataclasses import replace
+    from helpers import spec_for
+    from paper_1508_02899_amd import Lattice
+    bound = FP32_REL_L2 if dtype == "f32" else FP64_REL_L2
+    small = nx * ny * nv * nv < 1 << 20
+    for nsub in (2, 3, 4, 5):
+        f0, u, p = make_case(2, nx, nv, ny=ny, dtype=dtype, seed=nv + nsub,
+                             nsub=nsub, scheme=scheme)
+        spec = spec_for(f0, p, dtype)
+        ud = torch.from_numpy(u).cuda()
+        f = torch.from_numpy(f0).cuda()
+        with Lattice(spec) as lat:
+            lat.step(f, ud, p["tau_p"], p["kappa"], p["dt"], 1)
+            lat.sync()
+        if small:
+            err = rel_l2(f.cpu().numpy(), run_oracle(f0, u, p, 1))
+            say(f"  nsub {nsub}: rel L2 {err:.2e}")
+            assert err <= bound
+        if nsub in (2, 4):
+            g = torch.from_numpy(f0).cuda()
+            with Lattice(replace(spec, nsub=1)) as one:
+                one.step(g, ud, math.inf, 0.0, p["dt"], 1)
+                for _ in range(nsub):
+                    one.collide(g, ud, nsub * p["tau_p"], p["kappa"] / nsub,
+                                p["dt"], 1)
+                one.sync()
+            assert torch.equal(f, g)
+
+
+def test_2d_sub_steps_cfl_violation_leaves_f():
+    import torch
+    from helpers import spec_for
+    from paper_1508_02899_amd import Lattice, LatticeError
+    f0, u, p = make_case(2, 40, 17, ny=9, seed=5, nsub=3)
+    u[0, 1, 4, 7] = np.inf
+    f = torch.from_numpy(f0).cuda()
+    with Lattice(spec_for(f0, p, "f32")) as lat:
+        lat.step(f, torch.from_numpy(u).cuda(), p["tau_p"], p["kappa"],
+                 p["dt"], 2)
+        with pytest.raises(LatticeError):
+            lat.sync()
+    assert np.array_equal(f.cpu().numpy(), f0)
