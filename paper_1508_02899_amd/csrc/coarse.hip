@@ -1014,7 +1014,6 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ P
 // 16 faces per pass, the limited fluxes update the site's cells; the tile
 // is stored back.
 constexpr int kNVC = 17;
-constexpr int kTS = 32;
 
 // interior face id -> (axis, line, face): x-faces (line = row Jy, face k
 // between columns k-1 | k) first, then y-faces (line = column Jx)
@@ -1031,6 +1030,7 @@ __device__ __forceinline__ void face_of(int fid, int* axis, int* a, int* k) {
 // stay in registers, the biases come from LDS) and three workgroups' LDS
 // fit in a CU; the per-site steps are latency-bound, so the third
 // wavefront pays (measured: 13 % shorter passes than at two).
+template <int TS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 void k_mlp_correct17(
     CoarseGeom g, const float* __restrict__ P, const uint16_t* __restrict__ wq,
@@ -1038,24 +1038,24 @@ void k_mlp_correct17(
     const int* __restrict__ flag) {
   constexpr int NV = kNVC, N2 = NV * NV;
   constexpr int NFACE = 2 * NV * (NV - 1);
-  __shared__ float tile[N2][kTS + 1];
+  __shared__ float tile[N2][TS + 1];
   __shared__ float gx[4][NV][NV + 1];  // x-face fluxes [row][face 0..NV]
   __shared__ float gy[4][NV + 1][NV];  // y-face fluxes [face 0..NV][col]
   __shared__ uint16_t queue[4][NFACE];
-  __shared__ float us[2][kTS];  // flow at the tile's sites
+  __shared__ float us[2][TS];  // flow at the tile's sites
   __shared__ __align__(16) float bsh[2][kNH];  // hidden-layer biases
   if (*flag != 0) return;
   const int tid = (int)threadIdx.x, l = tid & 63, w = tid >> 6;
   const int64_t S = (int64_t)g.nx * g.ny;
-  const int64_t s0 = (int64_t)blockIdx.x * kTS;
-  const int nts = (int)((S - s0) < kTS ? (S - s0) : kTS);
+  const int64_t s0 = (int64_t)blockIdx.x * TS;
+  const int nts = (int)((S - s0) < TS ? (S - s0) : TS);
   // every load of a thread is issued before the first LDS write, so the
   // tile costs one memory latency, not one per element.  Thread tid moves
   // site ls of planes lj, lj + JP, ...; loads past the tile's end read
   // plane 0 of a valid site instead and are dropped
-  constexpr int JP = 256 / kTS, NL = (N2 + JP - 1) / JP;
-  static_assert(256 % kTS == 0, "whole planes per pass");
-  const int ls = tid % kTS, lj = tid / kTS;
+  constexpr int JP = 256 / TS, NL = (N2 + JP - 1) / JP;
+  static_assert(256 % TS == 0, "whole planes per pass");
+  const int ls = tid % TS, lj = tid / TS;
   const bool lsv = ls < nts;
   const float* const fsite = f + s0 + (lsv ? ls : 0);
   const size_t pstride = (size_t)JP * (size_t)S;
@@ -1067,8 +1067,8 @@ void k_mlp_correct17(
       v[it] = *(lj + JP * it < N2 ? p : fsite);
       p += pstride;
     }
-    if (tid < 2 * kTS) {
-      const int c = tid / kTS, s = tid - c * kTS;
+    if (tid < 2 * TS) {
+      const int c = tid / TS, s = tid - c * TS;
       us[c][s] = s < nts ? u[c * S + s0 + s] : 0.f;
     }
 #pragma unroll
@@ -1100,7 +1100,7 @@ void k_mlp_correct17(
     Pf[0] = 0.f;
     {
       const float* lp = &tile[rl ? la * NV : la][s];
-      const int lstep = (rl ? 1 : NV) * (kTS + 1);
+      const int lstep = (rl ? 1 : NV) * (TS + 1);
 #pragma unroll
       for (int j = 0; j < NV; ++j) Pf[j + 1] = Pf[j] + lp[j * lstep];
     }
@@ -1145,8 +1145,8 @@ void k_mlp_correct17(
       const int fid = live ? (int)queue[w][c0 + l] : 0;
       int axis, a, k;
       face_of(fid, &axis, &a, &k);
-      const int boff = __umul24(axis == 0 ? a * NV : a, kTS + 1);
-      const int soff = axis == 0 ? kTS + 1 : NV * (kTS + 1);
+      const int boff = __umul24(axis == 0 ? a * NV : a, TS + 1);
+      const int soff = axis == 0 ? TS + 1 : NV * (TS + 1);
       float st[5], ms, sg, anu;
       {
         auto ln = [&](int c) { return tcol[boff + __umul24(c, soff)]; };
@@ -1328,9 +1328,25 @@ hipError_t launch_mlp_correct(const CoarseGeom& g, const float* params,
                               const int* flag, hipStream_t s) {
   if (g.nv != kNVC) return hipErrorInvalidValue;
   const int64_t S = (int64_t)g.nx * g.ny;
-  const int grid = (int)((S + kTS - 1) / kTS);
-  hipLaunchKernelGGL(k_mlp_correct17, dim3(grid), dim3(256), 0, s, g, params,
-                     wq, f, u, flag);
+  auto go = [&](auto kernel, int ts) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((S + ts - 1) / ts)), dim3(256),
+                       0, s, g, params, wq, f, u, flag);
+  };
+  // A wavefront corrects its sites one after the other, so the tile is as
+  // small as still leaves the weights' loading a small share: the smaller the
+  // lattice, the more of the chip it then uses (two steps, us, threshold
+  // 8e-3, tiles of 32, 16, 8, 4 sites: 53 x 137 sites 318, 234, 210, 199;
+  // 128^2 398, 379, 347, 343; 180^2 638, 598, 592, 591; 240^2 1017, 938, 911,
+  // 940; 256^2 1057, 1020, 1047, 1059; 384^2 2166, 2168, 2208, 2291; 512^2
+  // 3774, 3819, 3858, 4094).
+  if (S <= 28000)
+    go(k_mlp_correct17<4>, 4);
+  else if (S <= 60000)
+    go(k_mlp_correct17<8>, 8);
+  else if (S <= 120000)
+    go(k_mlp_correct17<16>, 16);
+  else
+    go(k_mlp_correct17<32>, 32);
   return hipGetLastError();
 }
 

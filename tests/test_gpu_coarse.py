@@ -369,3 +369,51 @@ def test_correction_pass_matches_oracle_and_conserves_mass(n, ny):
     m.close()
     plain.close()
     corr.close()
+
+
+@pytest.mark.parametrize("nx,ny,kx,ky", [
+    (13, 5, 1, 1),      # tiles of 4 sites, one site left over
+    (41, 31, 5, 5),     # 31775 sites: tiles of 8, 7 left over
+    (41, 31, 7, 7),     # 62279: tiles of 16, 7 left over
+    (41, 31, 11, 9)])   # 125829: tiles of 32, 5 left over
+def test_correction_tiles_of_every_size(nx, ny, kx, ky):
+    """A periodic state repeated kx x ky times keeps its period, bit for bit,
+    through corrected steps, whatever tiles the lattice takes; one period
+    against the uncorrected step and the oracle at a few sites."""
+    import torch
+    from oracle import coarse as C
+    from paper_1508_02899_amd import Lattice, LatticeSpec, Mlp
+    rng = np.random.default_rng(nx * ky)
+    nv = 17
+    f0, _, u = _coarse_case(rng, nx, ny)
+    dx, dt, tau_p, St, eps = 2 * math.pi / 40, 0.05, 40.0, 1.5, 1e-3
+    P = _params(rng, 0.3)
+    m = Mlp()
+    m.set_params(_pack(P))
+
+    def run(sx, sy, steps, attach=True):
+        f = torch.from_numpy(f0).cuda().repeat(1, sy, sx).contiguous()
+        ud = torch.from_numpy(u[:1]).cuda().repeat(1, 1, sy, sx).contiguous()
+        with Lattice(LatticeSpec(dim=2, nx=sx * nx, ny=sy * ny, nv=nv, dx=dx,
+                                 vstride=4)) as lat:
+            if attach:
+                m.attach(lat, St, eps)
+            lat.step(f, ud, tau_p, 0.0, dt, steps)
+            lat.sync()
+        return f
+
+    one = run(1, 1, 2)
+    assert torch.equal(run(kx, ky, 2), one.repeat(1, ky, kx))
+    mid = run(1, 1, 1, attach=False).cpu().numpy().astype(np.float64)
+    got = run(1, 1, 1).cpu().numpy()
+    Pq = _unpack(_pack(P))
+    for y, x in ((0, 0), (ny - 1, nx - 1)):
+        c = mid[:, y, x]
+        Xo, ms, sg = C.face_features(c, nv, float(u[0, 0, y, x]),
+                                     float(u[0, 1, y, x]), 4 * dx / dt, dt,
+                                     tau_p, St)
+        yo, _ = C.forward(Pq, Xo)
+        want = C.corrected_site(c, nv, yo, ms, sg, line_eps=eps)
+        size = rel_l2(want, c)
+        assert rel_l2(got[:, y, x], want) < 2e-3 * max(1.0, size / 1e-2)
+    m.close()
