@@ -38,7 +38,11 @@ bool step2d_sub_large(int nv, int64_t pitch, int f64) {
 //   43.4, 63.8, 84.2 -> 23.3, 27.2, 30.8.  Past 8000 wavefronts (2500 in FP64)
 //   the stages compete for the compute units: 256^2 x 17^2 (8192) 52.8 ->
 //   56.5, 210 x 150 x 17^2 FP64 (12150) 123 -> 170.
-//   Large lattices, bound by memory: FP32 only (FP64 is bound by its
+//   FP64 upwind (little arithmetic to compete for) gains at every size:
+//   343 x 394 x 17^2 334, 495, 661 -> 205, 274, 369; 160 x 128 x 33^2 167,
+//   248, 329 -> 137, 161, 190; 400 x 300 x 9^2 53, 79, 103 -> 37, 55, 71,
+//   and with four stages 82, so up to three below 17^2.
+//   Large lattices, bound by memory: FP32 only (FP64 Koren is bound by its
 //   arithmetic).  65^2, 256^2 sites: 834, 1238, 1646 -> 737, 1272, 1359;
 //   33^2, 512^2 sites: 835, 1249, 1665 -> 737, 1474, 1632; upwind 823, 1238,
 //   1649 -> 559, 1008, 1097.  Three stages of two wavefronts leave two of the
@@ -60,6 +64,7 @@ int step2d_sub_take(const lattice_dims& d, int64_t left) {
     const int64_t S = 64 / P;
     const int64_t waves = (d.nx + S - 1) / S * d.ny;
     most = (d.f64 ? 2500 : 8000) / waves;
+    if (d.f64 && !d.koren && most < kSubMax) most = d.nv >= 17 ? kSubMax : 3;
     if (most > kSubMax) most = kSubMax;
   }
   if (most < 2) return 1;

@@ -705,3 +705,11 @@ def test_2d_sub_steps_cfl_violation_leaves_f():
         with pytest.raises(LatticeError):
             lat.sync()
     assert np.array_equal(f.cpu().numpy(), f0)
+
+
+@pytest.mark.parametrize("nv,nx,ny", [(5, 350, 401), (9, 203, 160),
+                                      (17, 150, 131), (33, 70, 45)])
+def test_2d_fp64_upwind_sub_steps_of_many_sites(nv, nx, ny):
+    """FP64 upwind lattices past 2500 wavefronts, whose sub-steps share a
+    pass there too."""
+    test_2d_sub_steps_in_one_pass(nv, "f64", nx, ny, "upwind")
