@@ -560,6 +560,18 @@ __global__ __launch_bounds__(64 * WGW) void k_step2d(
         ystep, yoff0, alpha_scale, beta, D, xg, w, y);
 }
 
+// Non-temporal stores when the state is larger than the 256 MB memory-side
+// cache (the next pass cannot find it there anyway) and the stored runs end
+// on 64-byte sectors: a sector that two tiles share has to wait in the L2
+// for its other half.  Koren, us per pass, non-temporal against ordinary:
+// 512^2 x 33^2 417, 440; 400 x 300 x 33^2 242, 248; 344 x 394 x 17^2 FP64
+// 143, 145; but 511 x 512 x 33^2 576, 498; 500 x 512 x 33^2 586, 489; 504 x
+// 512 x 33^2 483, 467; 700 x 600 x 17^2 252, 233.
+inline bool step2d_nt(const StepArgs& a, int nv, size_t elem) {
+  return (uint64_t)nv * nv * (uint64_t)a.pitch * elem > (256ull << 20) &&
+         (uint64_t)a.nx * elem % 64 == 0 && (uint64_t)a.pitch * elem % 64 == 0;
+}
+
 template <typename T, int NV, int P, int WGW, bool BIG>
 hipError_t launch_step2d_shape(const StepArgs& a, hipStream_t s) {
   constexpr int G = OutStage<T, NV, P, WGW>::G;
@@ -576,10 +588,7 @@ hipError_t launch_step2d_shape(const StepArgs& a, hipStream_t s) {
   const int ystep = a.shift % ny;
   const int yoff0 = (int)(((int64_t)a.shift * H) % ny);
   const T as = (T)a.alpha_scale, be = (T)a.beta, D = (T)a.D;
-  // non-temporal stores when the state is larger than the 256 MB
-  // memory-side cache (the next pass cannot find it there anyway)
-  const bool nt = (uint64_t)NV * NV * (uint64_t)a.pitch * sizeof(T) >
-                  (256ull << 20);
+  const bool nt = step2d_nt(a, NV, sizeof(T));
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * WGW), 0, s,
                        (const T*)a.fin, (T*)a.fout, (const T*)a.u, a.flag, nx,

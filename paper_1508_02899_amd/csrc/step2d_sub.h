@@ -269,8 +269,7 @@ hipError_t launch_step2d_sub_shape(const StepArgs& a, hipStream_t s) {
   const int ystep = a.shift % ny;
   const int yoff0 = (int)(((int64_t)a.shift * H) % ny);
   const T as = (T)a.alpha_scale, be = (T)a.beta, D = (T)a.D;
-  const bool nt = (uint64_t)NV * NV * (uint64_t)a.pitch * sizeof(T) >
-                  (256ull << 20);
+  const bool nt = step2d_nt(a, NV, sizeof(T));
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * WPS * a.nsub_inline),
                        0, s, (const T*)a.fin, (T*)a.fout, (const T*)a.u,
