@@ -514,6 +514,7 @@ __device__ __forceinline__ void step2d_tile(
 // consecutive rows, i.e. one stretch of memory per velocity plane instead
 // of one per XCD.  Blocks past the last full round of the 8 XCDs take the
 // contiguous ranges of xcd_remap.  A bijection of [0, n) for every g >= 1.
+// g may be the tiles of several rows (step2d_rows).
 __device__ __forceinline__ int xcd_rows(int b, int n, int g) {
   const int full = n / (8 * g) * (8 * g);
   if (b >= full) return full + xcd_remap(b - full, n - full);
@@ -532,7 +533,7 @@ __global__ __launch_bounds__(64 * WGW) void k_step2d(
     const T* __restrict__ fin, T* __restrict__ fout, const T* __restrict__ u,
     const int* __restrict__ flag, int nx, int ny, int64_t pitch, int shift,
     int xstep, int xoff0, int ystep, int yoff0, T alpha_scale, T beta, T D,
-    int ngx, int nblocks) {
+    int ngx, int nblocks, int rows) {
   using O = OutStage<T, NV, P, WGW>;
   constexpr int S = 64 / P;
   constexpr int H = (NV - 1) / 2;
@@ -543,7 +544,7 @@ __global__ __launch_bounds__(64 * WGW) void k_step2d(
   // 427 us per pass against 445 us with one contiguous range of rows per
   // XCD, whose eight bands of rows are far apart in every plane, and the
   // same time but 1.245x the HBM reads in plain dispatch order)
-  const int b = xcd_rows(blockIdx.x, nblocks, ngx);
+  const int b = xcd_rows(blockIdx.x, nblocks, ngx * rows);
   const int y = b / ngx;
   const int xg = b - y * ngx;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -560,6 +561,20 @@ __global__ __launch_bounds__(64 * WGW) void k_step2d(
         ystep, yoff0, alpha_scale, beta, D, xg, w, y);
 }
 
+// Rows of a plane start and end on 64-byte sectors.
+inline bool step2d_aligned(const StepArgs& a, size_t elem) {
+  return (uint64_t)a.nx * elem % 64 == 0 && (uint64_t)a.pitch * elem % 64 == 0;
+}
+
+// Spatial rows that follow each other on one XCD: four where rows share
+// sectors at their ends, so that three of four such sectors are written in
+// one L2 (Koren, us per pass, one row against four: 511 x 512 x 33^2 504, 476;
+// 500 x 512 x 33^2 491, 465; 343 x 394 x 17^2 FP64 152, 150; eight rows 475,
+// 470, 153), one elsewhere (512^2 x 33^2 415, 420).
+inline int step2d_rows(const StepArgs& a, size_t elem) {
+  return step2d_aligned(a, elem) ? 1 : 4;
+}
+
 // Non-temporal stores when the state is larger than the 256 MB memory-side
 // cache (the next pass cannot find it there anyway) and the stored runs end
 // on 64-byte sectors: a sector that two tiles share has to wait in the L2
@@ -569,7 +584,7 @@ __global__ __launch_bounds__(64 * WGW) void k_step2d(
 // 512 x 33^2 483, 467; 700 x 600 x 17^2 252, 233.
 inline bool step2d_nt(const StepArgs& a, int nv, size_t elem) {
   return (uint64_t)nv * nv * (uint64_t)a.pitch * elem > (256ull << 20) &&
-         (uint64_t)a.nx * elem % 64 == 0 && (uint64_t)a.pitch * elem % 64 == 0;
+         step2d_aligned(a, elem);
 }
 
 template <typename T, int NV, int P, int WGW, bool BIG>
@@ -593,7 +608,7 @@ hipError_t launch_step2d_shape(const StepArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * WGW), 0, s,
                        (const T*)a.fin, (T*)a.fout, (const T*)a.u, a.flag, nx,
                        ny, a.pitch, a.shift, xstep, xoff0, ystep, yoff0, as,
-                       be, D, ngx, nblocks);
+                       be, D, ngx, nblocks, step2d_rows(a, sizeof(T)));
   };
   if (BIG && nt) {
     if (a.koren)

@@ -225,12 +225,12 @@ __global__ __launch_bounds__(64 * WPS * kSubMax, 2) void k_step2d_sub(
     const T* __restrict__ fin, T* __restrict__ fout, const T* __restrict__ u,
     const int* __restrict__ flag, int nx, int ny, int64_t pitch, int shift,
     int xstep, int xoff0, int ystep, int yoff0, T alpha_scale, T beta, T D,
-    int ngx, int nblocks, int ns) {
+    int ngx, int nblocks, int rows, int ns) {
   using O = OutStage<T, NV, P, WPS>;
   constexpr int S = 64 / P;
   constexpr int H = (NV - 1) / 2;
   __shared__ T stage[2 * kSubMax * O::SIZE];
-  const int b = xcd_rows(blockIdx.x, nblocks, ngx);
+  const int b = xcd_rows(blockIdx.x, nblocks, ngx * rows);
   const int y = b / ngx;
   const int xg = b - y * ngx;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -274,7 +274,8 @@ hipError_t launch_step2d_sub_shape(const StepArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * WPS * a.nsub_inline),
                        0, s, (const T*)a.fin, (T*)a.fout, (const T*)a.u,
                        a.flag, nx, ny, a.pitch, a.shift, xstep, xoff0, ystep,
-                       yoff0, as, be, D, ngx, nblocks, a.nsub_inline);
+                       yoff0, as, be, D, ngx, nblocks,
+                       step2d_rows(a, sizeof(T)), a.nsub_inline);
   };
   if (BIG && nt) {
     if (a.koren)
