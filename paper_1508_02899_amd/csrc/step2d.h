@@ -286,17 +286,16 @@ __device__ __forceinline__ void step2d_tile(
     const T* __restrict__ fin, T* __restrict__ fout, const T* __restrict__ u,
     const int* __restrict__ flag, T* __restrict__ stage, int nx, int ny,
     size_t pitch, int shift, int xstep, int xoff0, int ystep, int yoff0,
-    T alpha_scale, T beta, T D, int xg, int w, int y) {
+    T alpha_scale, T beta, T D, int xb, int w, int y) {
   using K = Step2D<T, NV, P, KOREN>;
   using O = OutStage<T, NV, P, WGW>;
   constexpr int W = K::W, S = K::S, H = K::H, G = O::G;
   const int lane = (int)threadIdx.x & 63;
   const int p = lane / S;
   const int sl = lane - p * S;
-  const int x0 = xg * G + w * S;  // first site of this wavefront
-  int x = x0 + sl;
-  const bool active = x < nx;
-  if (!active) x = nx - 1;  // duplicate a real site; never stored
+  const int x0 = xb + w * S;  // first site of this wavefront
+  // outside the row: duplicate its first or last site
+  const int x = max(0, min(x0 + sl, nx - 1));
   const bool first = p == 0, last = p == P - 1;
   const int lane_l = lane - S, lane_r = lane + S;
   const int jx0 = p * (W - 1);  // first vx cell of this lane
@@ -359,8 +358,8 @@ __device__ __forceinline__ void step2d_tile(
   // Output of row t (the finished row t-3).  P == 1: a wavefront already
   // stores 64 consecutive sites per instruction.  P > 1: cells go to the
   // LDS buffer of t's parity; flush() then stores the workgroup's row.
-  // Lanes past the end of the spatial row hold a duplicate of site nx-1
-  // (same inputs, same operations, so the same bits) and store it there:
+  // Lanes outside the spatial row hold a duplicate of its first or last
+  // site (same inputs, same operations, so the same bits) and store it there:
   // every store is unconditional, which keeps the memory-counter waits
   // exact.
   // P == 1: offsets from the start of spatial row y (x is the clamped site,
@@ -373,10 +372,10 @@ __device__ __forceinline__ void step2d_tile(
   // flush: thread tid stores plane fj0 + P k, site fs of the workgroup
   const int fj0 = G >= 64 ? __builtin_amdgcn_readfirstlane(tid / G) : tid / G;
   const int fs = tid - (tid / G) * G;
-  const int fx = min(xg * G + fs, nx - 1);
+  const int fx = max(0, min(xb + fs, nx - 1));
   const uint32_t flane =
-      (uint32_t)(((size_t)fj0 * pitch + (size_t)(fx - xg * G)) * sizeof(T));
-  T* const frow0 = fout + (size_t)y * nx + (size_t)xg * G;
+      (uint32_t)(((size_t)fj0 * pitch + (size_t)(fx - xb)) * sizeof(T));
+  T* const frow0 = fout + ((int64_t)y * nx + xb);
   auto flush = [&](int t) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
@@ -533,7 +532,7 @@ __global__ __launch_bounds__(64 * WGW) void k_step2d(
     const T* __restrict__ fin, T* __restrict__ fout, const T* __restrict__ u,
     const int* __restrict__ flag, int nx, int ny, int64_t pitch, int shift,
     int xstep, int xoff0, int ystep, int yoff0, T alpha_scale, T beta, T D,
-    int ngx, int nblocks, int rows) {
+    int ngx, int nblocks, int rows, int sector) {
   using O = OutStage<T, NV, P, WGW>;
   constexpr int S = 64 / P;
   constexpr int H = (NV - 1) / 2;
@@ -548,17 +547,18 @@ __global__ __launch_bounds__(64 * WGW) void k_step2d(
   const int y = b / ngx;
   const int xg = b - y * ngx;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int x0 = xg * O::G + w * S;
+  const int xb = xg * O::G - ((y * nx) & sector);  // the tile's first site
+  const int x0 = xb + w * S;
   const bool interior = x0 + S <= nx && x0 - shift * H >= 0 &&
                         x0 + S - 1 + shift * H <= nx - 1;
   if (interior)
     step2d_tile<T, NV, P, KOREN, true, WGW, NT>(
         fin, fout, u, flag, stage, nx, ny, (size_t)pitch, shift, xstep, xoff0,
-        ystep, yoff0, alpha_scale, beta, D, xg, w, y);
+        ystep, yoff0, alpha_scale, beta, D, xb, w, y);
   else
     step2d_tile<T, NV, P, KOREN, false, WGW, NT>(
         fin, fout, u, flag, stage, nx, ny, (size_t)pitch, shift, xstep, xoff0,
-        ystep, yoff0, alpha_scale, beta, D, xg, w, y);
+        ystep, yoff0, alpha_scale, beta, D, xb, w, y);
 }
 
 // Rows of a plane start and end on 64-byte sectors.
@@ -573,6 +573,21 @@ inline bool step2d_aligned(const StepArgs& a, size_t elem) {
 // 470, 153), one elsewhere (512^2 x 33^2 415, 420).
 inline int step2d_rows(const StepArgs& a, size_t elem) {
   return step2d_aligned(a, elem) ? 1 : 4;
+}
+
+// Tiles whose edges inside a row lie on 64-byte sectors of the planes: the
+// tiles of row y start (y nx) & sector sites early.  Taken (else 0) where
+// that needs no further tile (us per pass, 0 against this: 700 x 600 x 17^2
+// 229, 222, upwind 249, 224; 504 x 512 x 33^2 450, 444; 500 x 512 x 33^2
+// upwind 465, 457; odd widths within 1 %).
+inline int step2d_sector(const StepArgs& a, int G, size_t elem) {
+  const int64_t n = 64 / (int64_t)elem;
+  int64_t g = n;  // row starts are multiples of g sites from a sector
+  while (a.nx % g) g /= 2;
+  if ((uint64_t)a.pitch * elem % 64 != 0 ||
+      (a.nx + n - g + G - 1) / G != (a.nx + G - 1) / G)
+    return 0;
+  return (int)n - 1;
 }
 
 // Non-temporal stores when the state is larger than the 256 MB memory-side
@@ -608,7 +623,8 @@ hipError_t launch_step2d_shape(const StepArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * WGW), 0, s,
                        (const T*)a.fin, (T*)a.fout, (const T*)a.u, a.flag, nx,
                        ny, a.pitch, a.shift, xstep, xoff0, ystep, yoff0, as,
-                       be, D, ngx, nblocks, step2d_rows(a, sizeof(T)));
+                       be, D, ngx, nblocks, step2d_rows(a, sizeof(T)),
+                       step2d_sector(a, G, sizeof(T)));
   };
   if (BIG && nt) {
     if (a.koren)

@@ -33,16 +33,16 @@ __device__ __forceinline__ void step2d_sub_wave(
     const T* __restrict__ fin, T* __restrict__ fout, const T* __restrict__ u,
     const int* __restrict__ flag, T* __restrict__ stage, int nx, int ny,
     size_t pitch, int shift, int xstep, int xoff0, int ystep, int yoff0,
-    T alpha_scale, T beta, T D, int xg, int w, int y, int q, int ns) {
+    T alpha_scale, T beta, T D, int xb, int w, int y, int q, int ns) {
   using K = Step2D<T, NV, P, KOREN>;
   using O = OutStage<T, NV, P, WPS>;
   constexpr int W = K::W, S = K::S, H = K::H, G = O::G;
   const int lane = (int)threadIdx.x & 63;
   const int p = lane / S;
   const int sl = lane - p * S;
-  const int x0 = xg * G + w * S;  // first site of this wavefront
-  int x = x0 + sl;
-  if (x >= nx) x = nx - 1;  // duplicate a real site
+  const int x0 = xb + w * S;  // first site of this wavefront
+  // outside the row: duplicate its first or last site
+  const int x = max(0, min(x0 + sl, nx - 1));
   const bool first = p == 0, last = p == P - 1;
   const int lane_l = lane - S, lane_r = lane + S;
   const int jx0 = p * (W - 1);  // first vx cell of this lane
@@ -113,10 +113,10 @@ __device__ __forceinline__ void step2d_sub_wave(
   const int tid = (int)threadIdx.x;
   const int PR = ns * P;
   const int fj0 = tid / G, fs = tid - fj0 * G;
-  const int fx = min(xg * G + fs, nx - 1);
+  const int fx = max(0, min(xb + fs, nx - 1));
   const uint32_t flane =
-      (uint32_t)(((size_t)fj0 * pitch + (size_t)(fx - xg * G)) * sizeof(T));
-  T* const frow0 = fout + (size_t)y * nx + (size_t)xg * G;
+      (uint32_t)(((size_t)fj0 * pitch + (size_t)(fx - xb)) * sizeof(T));
+  T* const frow0 = fout + ((int64_t)y * nx + xb);
   const uint32_t slot_bytes = (uint32_t)(pitch * sizeof(T));
   const T* const fin_stage =
       stage + 2 * (ns - 1) * O::SIZE + fj0 * O::STRIDE + fs;
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(64 * WPS * kSubMax, 2) void k_step2d_sub(
     const T* __restrict__ fin, T* __restrict__ fout, const T* __restrict__ u,
     const int* __restrict__ flag, int nx, int ny, int64_t pitch, int shift,
     int xstep, int xoff0, int ystep, int yoff0, T alpha_scale, T beta, T D,
-    int ngx, int nblocks, int rows, int ns) {
+    int ngx, int nblocks, int rows, int sector, int ns) {
   using O = OutStage<T, NV, P, WPS>;
   constexpr int S = 64 / P;
   constexpr int H = (NV - 1) / 2;
@@ -235,21 +235,22 @@ __global__ __launch_bounds__(64 * WPS * kSubMax, 2) void k_step2d_sub(
   const int xg = b - y * ngx;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int q = wv / WPS, w = wv - q * WPS;
-  const int x0 = xg * O::G + w * S;
+  const int xb = xg * O::G - ((y * nx) & sector);  // the tile's first site
+  const int x0 = xb + w * S;
   const bool interior = x0 + S <= nx && x0 - shift * H >= 0 &&
                         x0 + S - 1 + shift * H <= nx - 1;
   if (q > 0)
     step2d_sub_wave<T, NV, P, KOREN, true, false, WPS, NT>(
         fin, fout, u, flag, stage, nx, ny, (size_t)pitch, shift, xstep, xoff0,
-        ystep, yoff0, alpha_scale, beta, D, xg, w, y, q, ns);
+        ystep, yoff0, alpha_scale, beta, D, xb, w, y, q, ns);
   else if (interior)
     step2d_sub_wave<T, NV, P, KOREN, true, true, WPS, NT>(
         fin, fout, u, flag, stage, nx, ny, (size_t)pitch, shift, xstep, xoff0,
-        ystep, yoff0, alpha_scale, beta, D, xg, w, y, 0, ns);
+        ystep, yoff0, alpha_scale, beta, D, xb, w, y, 0, ns);
   else
     step2d_sub_wave<T, NV, P, KOREN, false, true, WPS, NT>(
         fin, fout, u, flag, stage, nx, ny, (size_t)pitch, shift, xstep, xoff0,
-        ystep, yoff0, alpha_scale, beta, D, xg, w, y, 0, ns);
+        ystep, yoff0, alpha_scale, beta, D, xb, w, y, 0, ns);
 }
 
 template <typename T, int NV, int P, int WPS, bool BIG>
@@ -275,7 +276,8 @@ hipError_t launch_step2d_sub_shape(const StepArgs& a, hipStream_t s) {
                        0, s, (const T*)a.fin, (T*)a.fout, (const T*)a.u,
                        a.flag, nx, ny, a.pitch, a.shift, xstep, xoff0, ystep,
                        yoff0, as, be, D, ngx, nblocks,
-                       step2d_rows(a, sizeof(T)), a.nsub_inline);
+                       step2d_rows(a, sizeof(T)),
+                       step2d_sector(a, G, sizeof(T)), a.nsub_inline);
   };
   if (BIG && nt) {
     if (a.koren)

@@ -102,3 +102,31 @@ def test_padded_no_alloc_step():
     assert int(status.item()) == 0
     assert np.array_equal(f.cpu().numpy(), want)
     assert np.isnan(_gaps(sp, buf)).all()
+
+
+@pytest.mark.parametrize("nv,dtype,nx,ny,nsub,scheme", [
+    (5, "f32", 201, 33, 1, "koren"), (7, "f32", 41, 3, 1, "upwind"),
+    (9, "f64", 119, 21, 1, "koren"), (13, "f32", 210, 150, 1, "upwind"),
+    (17, "f32", 301, 257, 1, "koren"), (17, "f64", 181, 70, 1, "koren"),
+    (33, "f32", 237, 161, 1, "koren"), (33, "f64", 110, 9, 1, "upwind"),
+    (65, "f32", 75, 41, 1, "koren"), (9, "f32", 103, 31, 3, "koren"),
+    (17, "f64", 9, 5, 2, "upwind"), (33, "f32", 205, 161, 2, "upwind"),
+    (65, "f32", 97, 83, 4, "koren"), (3, "f32", 1, 1, 1, "koren")])
+def test_tiles_that_start_on_sectors(nv, dtype, nx, ny, nsub, scheme):
+    """Planes on 256-byte boundaries, where tiles of a row may start early to
+    lie on 64-byte sectors, against contiguous planes of odd length, where
+    none does: the same bits."""
+    import torch
+    from paper_1508_02899_amd import Lattice
+    f0, u, p = make_case(2, nx, nv, ny=ny, dtype=dtype, seed=nv + nx,
+                         nsub=nsub, scheme=scheme)
+    out = []
+    for pad in (0, -(nx * ny) % 64):
+        sp, buf, f = _padded(spec_for(f0, p, dtype), f0, pad)
+        with Lattice(sp) as lat:
+            lat.step(f, torch.from_numpy(u).cuda(), p["tau_p"], p["kappa"],
+                     p["dt"], 2)
+            lat.sync()
+        assert np.isnan(_gaps(sp, buf)).all()
+        out.append(f.contiguous())
+    assert torch.equal(*out)
