@@ -91,7 +91,8 @@ def kernel_hash(dim: int) -> str:
 def step_kernel(dim, n, nv, dtype):
     """The step kernel the library runs for this lattice (2D: k_step2d; 1D:
     the split-column pass up to 2^19 sites for the velocity counts it is
-    built for, else one lane per site)."""
+    built for, else one lane per site; short 1D lattices take several steps
+    per launch with the same update)."""
     if dim == 2:
         return "k_step2d"
     parts = nv in (17, 33, 65) or (nv == 129 and dtype == "f32")
@@ -897,9 +898,9 @@ def main():
     ev3.record()
     torch.cuda.synchronize()
     lat.sync()
-    # a 2D step is nsub passes (the later ones collision only), each
-    # reading and writing the whole state; a 1D step is one launch
-    kern2_ms, launches = ev2.elapsed_time(ev3), K * (nsub if dim == 2 else 1)
+    # a step reads and writes the state at least once; the library may make
+    # several passes of its sub-steps, or one launch of several short steps
+    kern2_ms, launches = ev2.elapsed_time(ev3), K
     if args.copy_calibration:
         g = spec.empty_state()
         lat.copy_state(g, f)
