@@ -23,17 +23,17 @@
 
 namespace lat {
 
-// Finished sites G, sites loaded at most, wavefronts of a workgroup.  32
+// Finished sites G, sites loaded at most.  32
 // sites spread a short lattice over the most compute units; from 257 such
 // workgroups on, 64 sites recompute less (16384 x 33 FP64: 4.3 us a step with
 // 32, 2.7 with 64; 256 x 33 FP64: 2.2 with 32, 2.4 with 64).
 template <int G>
 struct MultiTile;
 template <> struct MultiTile<32> {
-  static constexpr int REGION = 160, WAVES = 8;
+  static constexpr int REGION = 160;
 };
 template <> struct MultiTile<64> {
-  static constexpr int REGION = 192, WAVES = 16;
+  static constexpr int REGION = 192;
 };
 
 // Velocity lattices with a kernel and the parts of their columns (lanes of
@@ -48,6 +48,16 @@ constexpr int multi_parts(int nv) {
   }
 }
 
+// Wavefronts of a workgroup: 16 where 8 would go over a region in three
+// rounds, being 8 sites each (25 and 33 velocities at G = 32; us a step, 8
+// against 16, 256 sites: 33 FP64 2.19, 2.14, FP32 with 3 sub-steps 2.39, 2.18;
+// 25 FP64 1.87, 1.80, FP32 1.44, 1.36; but 5 FP64 0.74, 0.75, 17 FP64 1.33,
+// 1.36), and for G = 64.
+template <int G>
+constexpr int multi_waves(int nv) {
+  return G == 64 || multi_parts(nv) == 8 ? 16 : 8;
+}
+
 // Steps per launch: as many as the region allows, at most 16.
 template <int G>
 constexpr int multi_steps(int nv, int shift) {
@@ -57,12 +67,12 @@ constexpr int multi_steps(int nv, int shift) {
 }
 
 template <typename T, int NV, int G, bool KOREN>
-__global__ __launch_bounds__(64 * MultiTile<G>::WAVES) void k_step1d_multi(
+__global__ __launch_bounds__(64 * multi_waves<G>(NV)) void k_step1d_multi(
     const T* __restrict__ fin, T* __restrict__ fout, const T* __restrict__ u,
     const int* __restrict__ flag, int nx, int shift, int nsub, T alpha_scale,
     T beta, T D, int nsteps, int64_t step0, int64_t u_hold, int nblocks) {
   constexpr int P = multi_parts(NV);
-  constexpr int REGION = MultiTile<G>::REGION, WAVES = MultiTile<G>::WAVES;
+  constexpr int REGION = MultiTile<G>::REGION, WAVES = multi_waves<G>(NV);
   using PT = Parts1DTile<T, NV, P, WAVES>;
   constexpr int W = PT::W, S = PT::S, H = PT::H;
   constexpr int PITCH = REGION + 2;
@@ -148,7 +158,7 @@ hipError_t launch_multi_g(const StepArgs& a, int nsteps, int64_t step0,
   const int nblocks = (int)((a.nx + G - 1) / G);
   const T as = (T)a.alpha_scale, be = (T)a.beta, D = (T)a.D;
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * MultiTile<G>::WAVES), 0, s,
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * multi_waves<G>(NV)), 0, s,
                        (const T*)a.fin, (T*)a.fout, (const T*)a.u, a.flag,
                        (int)a.nx, a.shift, a.nsub_inline, as, be, D, nsteps,
                        step0, u_hold, nblocks);
