@@ -213,15 +213,18 @@ void density_go(const T* f, int64_t sites, int64_t pitch, int nplanes,
 
 // Flow check: flag |= 1 if some |u| exceeds umax_ok (>= when strict) or is
 // not finite.  Grid-stride, one atomic per offending wavefront.
-// With n16 > 0 also the copy of n16 16-byte pieces that a call of an odd
-// number of passes starts with: one launch instead of two, which is what a
+// With n16 > 0 also the copy of n16 16-byte pieces and tail more bytes that a
+// call of an odd number of passes starts with: one launch instead of two, which is what a
 // call of a single step on a small lattice consists of.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_cfl_check(
     const T* __restrict__ u, int64_t n, T umax_ok, int strict,
     int* __restrict__ flag, const uint4* __restrict__ src,
-    uint4* __restrict__ dst, int64_t n16) {
+    uint4* __restrict__ dst, int64_t n16, int tail) {
   bool bad = false;
+  if (blockIdx.x == 0 && (int)threadIdx.x < tail)
+    ((char*)(dst + n16))[threadIdx.x] =
+        ((const char*)(src + n16))[threadIdx.x];
   const int64_t stride = (int64_t)gridDim.x * kBlock;
   for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n16;
        i += stride)
@@ -322,22 +325,22 @@ hipError_t launch_density(const void* f, int64_t sites, int64_t pitch,
 hipError_t launch_check_copy(const void* u, int64_t n, double umax_ok,
                              int strict, int f64, int* flag, void* dst,
                              const void* src, int64_t bytes, hipStream_t s) {
-  const bool whole = bytes % 16 == 0 && ((uintptr_t)dst % 16) == 0 &&
-                     ((uintptr_t)src % 16) == 0;
-  if (!whole) {  // ragged copies by themselves
+  const bool whole = ((uintptr_t)dst % 16) == 0 && ((uintptr_t)src % 16) == 0;
+  if (!whole) {  // misaligned copies by themselves
     const hipError_t e = launch_copy(dst, src, bytes, s);
     if (e != hipSuccess) return e;
   }
   const int64_t n16 = whole ? bytes / 16 : 0;
+  const int tail = whole ? (int)(bytes % 16) : 0;
   const int g = grid_for(n > n16 ? n : n16);
   if (f64)
     hipLaunchKernelGGL(k_cfl_check<double>, dim3(g), dim3(kBlock), 0, s,
                        (const double*)u, n, umax_ok, strict, flag,
-                       (const uint4*)src, (uint4*)dst, n16);
+                       (const uint4*)src, (uint4*)dst, n16, tail);
   else
     hipLaunchKernelGGL(k_cfl_check<float>, dim3(g), dim3(kBlock), 0, s,
                        (const float*)u, n, (float)umax_ok, strict, flag,
-                       (const uint4*)src, (uint4*)dst, n16);
+                       (const uint4*)src, (uint4*)dst, n16, tail);
   return hipGetLastError();
 }
 
