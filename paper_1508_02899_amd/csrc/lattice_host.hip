@@ -297,16 +297,24 @@ static int run_call(const lattice_desc& d, CallPlan& p, void* f,
     }
     return true;
   };
-  // Short 1D lattices: several steps per launch, spread evenly over an even
-  // number of launches (no copy needed) unless there is only one step;
-  // profiled runs time every step by itself.
+  // Short 1D lattices: several steps per launch, spread evenly over the
+  // launches; profiled runs time every step by itself.  An odd number of
+  // launches starts from a copy, which the flow check's launch makes where
+  // both buffers are 16-byte aligned: cheaper than one more launch while the
+  // state is small (a call of 2 and 5 steps,
+  // us, a further launch against the copy: 0.5 MB, 8192 x 17, 12.2, 12.5 ->
+  // 9.0, 8.9; 2.1 MB, 8192 x 33 FP64, 11.5, 14.4 -> 9.1, 14.2; 4.3 MB, 32768 x
+  // 17 FP64, 11.6, 21.6 -> 14.2, 20.6).
+  constexpr int64_t kCheapCopy = 5 << 19;
   int64_t launches = p.passes;
   if (d.dim == 1 && stream && nsteps > 1 && !(L && L->prof)) {
     const int64_t most =
         lat::step1d_multi_steps(d.nv, d.nx, d.vstride, d.nsub, p.a.f64);
     if (most > 1) {
       launches = (nsteps + most - 1) / most;
-      launches += launches & 1;
+      const bool along = p.used > 0 && state_bytes <= kCheapCopy &&
+                         ((uintptr_t)f | (uintptr_t)twin) % 16 == 0;
+      if (!along) launches += launches & 1;
     }
   }
   void* bufs[2] = {f, twin};
