@@ -29,10 +29,14 @@ __device__ __forceinline__ double koren(double dp, double dm) {
   return fmax(lo, fmin(hi, 0.0));
 }
 
+// One rounding, and no more: a factor that is known to be 1 turns the call
+// into an addition, which must not be contracted with what made an operand.
 __device__ __forceinline__ float fma_t(float a, float b, float c) {
+#pragma clang fp contract(off)
   return __builtin_fmaf(a, b, c);
 }
 __device__ __forceinline__ double fma_t(double a, double b, double c) {
+#pragma clang fp contract(off)
   return __builtin_fma(a, b, c);
 }
 

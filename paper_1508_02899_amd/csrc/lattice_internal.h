@@ -47,6 +47,9 @@ hipError_t launch_step1d_parts(const StepArgs& a, hipStream_t s);
 // launch of steps step0 .. step0 + nsteps - 1 of a call; a.u is slice 0.
 constexpr int64_t kMultiSmall = 32 * 256;  // 32-site tiles, one per CU
 int step1d_multi_steps(int nv, int64_t nx, int shift, int nsub, int f64);
+// The lattices that have it, whatever the shift: their one-step passes use
+// its arithmetic, so that the bits do not depend on how a run is cut.
+bool step1d_multi_lattice(int nv, int64_t nx, int nsub, int f64);
 hipError_t launch_step1d_multi(const StepArgs& a, int nsteps, int64_t step0,
                                int64_t u_hold, hipStream_t s);
 hipError_t launch_step2d(const StepArgs& a, hipStream_t s);

@@ -178,7 +178,7 @@ struct Parts1DTile {
 #pragma clang fp contract(off)
     const int lane = (int)threadIdx.x & 63;
     const int p = lane / S;
-    const bool first = p == 0, last = p == P - 1;
+    const bool first = P == 1 || p == 0, last = P == 1 || p == P - 1;
     const int lane_l = lane - S, lane_r = lane + S;
     const int j0 = p * (W - 1);
     T nup[W + 2], num[W + 2];  // split coefficients of cells -1 .. W
@@ -194,10 +194,13 @@ struct Parts1DTile {
       // empty past the ends of the velocity axis)
       T gp[W + 2], gm[W + 2];
       {
-        const T l1 = lane_read(c[W - 2], lane_l);
-        const T r0 = lane_read(c[1], lane_r);
-        const T cl = first ? T(0) : l1;
-        const T cr = last ? T(0) : r0;
+        T cl = T(0), cr = T(0);
+        if constexpr (P > 1) {
+          const T l1 = lane_read(c[W - 2], lane_l);
+          const T r0 = lane_read(c[1], lane_r);
+          cl = first ? T(0) : l1;
+          cr = last ? T(0) : r0;
+        }
         gp[0] = nup[0] * cl;
         gm[0] = num[0] * cl;
 #pragma unroll
@@ -220,7 +223,8 @@ struct Parts1DTile {
                 koren(gm[f] - gm[f + 1], gm[f + 1] - gm[f + 2]);
         F[f] = fl;
       }
-      {
+      F[0] = F[W] = T(0);
+      if constexpr (P > 1) {
         const T fl = lane_read(F[W - 1], lane_l);
         const T fr = lane_read(F[1], lane_r);
         F[0] = first ? T(0) : fl;
@@ -231,8 +235,11 @@ struct Parts1DTile {
       for (int i = 0; i < W; ++i) q[i] = c[i] - (F[i + 1] - F[i]);
 
       // diffusion: face difference q_{f-1} - q_f, zero at the outer faces
-      const T al = lane_read(q[W - 2], lane_l);
-      const T ar = lane_read(q[1], lane_r);
+      T al = T(0), ar = T(0);
+      if constexpr (P > 1) {
+        al = lane_read(q[W - 2], lane_l);
+        ar = lane_read(q[1], lane_r);
+      }
       T df[W + 1];
 #pragma unroll
       for (int f = 0; f <= W; ++f) {

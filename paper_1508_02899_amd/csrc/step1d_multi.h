@@ -10,8 +10,9 @@
 // sites and updates a region that shrinks by h s on either side per step.
 // The neighbours compute the same halo sites again from the same values with
 // the same operations; no workgroup waits for another.  The update is the
-// split-column one (parts1d.h), for nv = 17 and 33 bit for bit that of the
-// one-step pass.  Measured per step of a long call (one launch per step
+// split-column one (parts1d.h), bit for bit that of the one-step pass of the
+// same lattice (step1d_parts.hip, or step1d.hip with the same arithmetic).
+// Measured per step of a long call (one launch per step
 // before): 256 x 33 FP64 4.35 -> 2.24 us, 256 x 17 FP32 3.1 -> 1.0, 4096 x 9
 // FP32 3.85 -> 0.74, 16384 x 33 FP32 3.6 -> 1.7.  What is left is the update
 // of the region by one compute unit and, per launch, one load and one store

@@ -713,3 +713,43 @@ def test_2d_fp64_upwind_sub_steps_of_many_sites(nv, nx, ny):
     """FP64 upwind lattices past 2500 wavefronts, whose sub-steps share a
     pass there too."""
     test_2d_sub_steps_in_one_pass(nv, "f64", nx, ny, "upwind")
+
+
+@pytest.mark.parametrize("nx,nsub,scheme", [(301, 1, "koren"),
+                                            (97, 3, "upwind")])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("nv", [3, 5, 7, 9, 11, 13, 17, 21, 25, 33, 45, 65])
+def test_1d_bits_do_not_depend_on_the_call(nv, dtype, nx, nsub, scheme):
+    """The same bits from one call of n steps, n calls of one step, a call
+    with profiling on, a state that is not 16-byte aligned and the step that
+    allocates nothing: several passes serve them, with one arithmetic."""
+    import torch
+    from helpers import spec_for
+    from paper_1508_02899_amd import Lattice
+    from paper_1508_02899_amd.lattice import step_noalloc
+    f0, u, p = make_case(1, nx, nv, dtype=dtype, seed=nx + nv, nsub=nsub,
+                         scheme=scheme)
+    spec = spec_for(f0, p, dtype)
+    start, ud = torch.from_numpy(f0).cuda(), torch.from_numpy(u).cuda()
+    args = (p["tau_p"], p["kappa"], p["dt"])
+    with Lattice(spec) as lat:
+        def call(nsteps, off=0):
+            buf = torch.empty(start.numel() + off, dtype=start.dtype,
+                              device="cuda")
+            f = buf[off:].view(start.shape)
+            f.copy_(start)
+            lat.step(f, ud, *args, nsteps)
+            lat.sync()
+            return f
+        ref = start.clone()
+        for n in range(1, 8):
+            lat.step(ref, ud, *args, 1)
+            lat.sync()
+            for off in (0, 1):
+                assert torch.equal(call(n, off), ref), f"{n} steps, {off}"
+        lat.profile(True)
+        assert torch.equal(call(7), ref)
+        lat.profile(False)
+    f = start.clone()
+    step_noalloc(spec, f, ud, *args, 7)
+    assert torch.equal(f, ref)
