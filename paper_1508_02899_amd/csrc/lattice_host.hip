@@ -208,8 +208,8 @@ struct CallPlan {
   int64_t used = 0;        // u slices the device check reads
   double umax_ok = 0.0;    // |u| bound of Eq. 3 for this call
   lat::lattice_dims dims = {};  // 2D
-  int64_t passes_per_step = 1;
   int64_t passes = 0;
+  bool cut = false;  // the first pass of the first step in two
 };
 
 static int plan_call(const lattice_desc& d, int64_t sites, size_t elem,
@@ -256,15 +256,19 @@ static int plan_call(const lattice_desc& d, int64_t sites, size_t elem,
   p->used = drag ? need : 0;
   // per step, 1D does everything in one pass (nsub inline); 2D does one
   // streaming pass and further collision-only passes, each with as many of
-  // the sub-steps as step2d_sub_take gives it.
+  // the sub-steps as step2d_sub_take gives it.  An odd number of passes needs
+  // a copy of the state, which one more pass saves (step2d_sub_cut).
+  p->passes = nsteps;
   if (d.dim == 2) {
     p->dims = {d.nv, d.dtype == LATTICE_F64, d.scheme == LATTICE_KOREN, d.nx,
                d.ny, plane_pitch_of(d)};
-    p->passes_per_step = 0;
-    for (int64_t left = d.nsub; left > 0; ++p->passes_per_step)
+    int64_t per_step = 0;
+    for (int64_t left = d.nsub; left > 0; ++per_step)
       left -= lat::step2d_sub_take(p->dims, left);
+    p->passes = nsteps * per_step;
+    p->cut = p->passes % 2 != 0 && lat::step2d_sub_cut(p->dims, d.nsub);
+    p->passes += p->cut;
   }
-  p->passes = nsteps * p->passes_per_step;
   lat::StepArgs& a = p->a;
   a.nx = d.nx;
   a.ny = d.ny;
@@ -356,14 +360,17 @@ static int run_call(const lattice_desc& d, CallPlan& p, void* f,
     const int64_t sl = d.u_hold > 0 ? s / d.u_hold : 0;
     a.u = (const char*)u + (size_t)(sl * p.slice_len) * elem;
     int64_t left = d.nsub;
-    for (int64_t ps = 0; ps < p.passes_per_step; ++ps, ++k) {
+    int rest = 0;  // sub-steps of a pass in two that its second half takes
+    for (bool head = true; left > 0; head = false, ++k) {
       a.fin = bufs[k & 1];
       a.fout = bufs[(k + 1) & 1];
-      a.shift = (ps == 0 && stream) ? d.vstride : 0;
+      a.shift = head && stream ? d.vstride : 0;
       if (d.dim == 2) {  // this pass's share of the sub-steps
-        a.nsub_inline = lat::step2d_sub_take(p.dims, left);
-        left -= a.nsub_inline;
+        a.nsub_inline = rest > 0 ? rest : lat::step2d_sub_take(p.dims, left);
+        rest = head && s == 0 && p.cut ? a.nsub_inline / 2 : 0;
+        a.nsub_inline -= rest;
       }
+      left -= a.nsub_inline;
       if (L && !chk(record_pair(L, false), "event record")) return LATTICE_EHIP;
       hipError_t e = d.dim == 1           ? lat::launch_step1d(a, st)
                      : a.nsub_inline > 1 ? lat::launch_step2d_sub(a, st)

@@ -55,13 +55,16 @@ hipError_t launch_step1d_multi(const StepArgs& a, int nsteps, int64_t step0,
 hipError_t launch_step2d(const StepArgs& a, hipStream_t s);
 // One pass with a.nsub_inline >= 2 collision sub-steps; step2d_sub_take: how
 // many of the sub-steps left the next pass takes (1: launch_step2d);
-// step2d_sub_large: past the caches, in the wider shape.
+// step2d_sub_large: past the caches, in the wider shape; step2d_sub_cut:
+// whether a call of an odd number of passes takes its first pass in two
+// rather than start from a copy of the state.
 struct lattice_dims {
   int nv, f64, koren;
   int64_t nx, ny, pitch;
 };
 int step2d_sub_take(const lattice_dims& d, int64_t left);
 bool step2d_sub_large(int nv, int64_t pitch, int f64);
+bool step2d_sub_cut(const lattice_dims& d, int64_t nsub);
 hipError_t launch_step2d_sub(const StepArgs& a, hipStream_t s);
 
 // Sticky CFL / finiteness check of the u slices: sets flag |= 1 when some

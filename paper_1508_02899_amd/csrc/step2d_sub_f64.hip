@@ -1,5 +1,7 @@
 // step2d_sub_f64.hip -- FP64 2D passes with several sub-steps, and the rule
 // that says how many a pass takes.
+#include <math.h>
+
 #include "step2d_sub.h"
 
 namespace lat {
@@ -70,6 +72,47 @@ int step2d_sub_take(const lattice_dims& d, int64_t left) {
   if (most < 2) return 1;
   const int64_t passes = (left + most - 1) / most;
   return (int)((left + passes - 1) / passes);
+}
+
+// A call of an odd number of passes starts from a copy of the state in the
+// twin.  Where the first pass takes several sub-steps it can go in two halves
+// instead (1 + 1, 2 + 1, 2 + 2): one more pass and no copy.  The copy grows
+// with the state; the pass of a small lattice is a chain of nv + 3 rows, each
+// longer with nv.  Measured (one step, Koren and 2 sub-steps unless said, us,
+// copy against two halves; the line 250 kB nv^1.5 was fitted to 896 such
+// pairs of nv 5 to 65 and 2 to 1100 MB, of which it misses the better one by
+// 1 % on average):
+//   below it  62 x 47 x 13^2 (2 MB) 15.2, 21.2; 57 x 42 x 25^2 (6 MB) 27.1,
+//             37.3; 64 x 42 x 65^2 (45 MB) 79.2, 91.5, 4 sub-steps 87.8, 116
+//   near it   155 x 119 x 9^2 (6 MB) 18.3, 19.8; 134 x 103 x 17^2 (16 MB)
+//             30.5, 32.8, 4 sub-steps 54.3, 43.6; 109 x 84 x 33^2 (40 MB)
+//             51.1, 54.9, 4 sub-steps 0.93 times
+//   above it  281 x 215 x 17^2 (70 MB) 74, 54; 256 x 197 x 33^2 (220 MB) 259,
+//             196; 1408 x 1074 x 5^2 (151 MB) 175, 124; 768 x 581 x 25^2 (1.1
+//             GB) 1323, 923, upwind 989, 911; 304 x 223 x 65^2 (1.1 GB) 1285,
+//             1030, 4 sub-steps 1968, 1564; FP64 upwind 240 x 182 x 17^2 (101
+//             MB) 80.6, 66.7; but 130 x 100 x 65^2 (three ragged tiles a row)
+//             274, 342
+// Two exceptions in FP32.  Between 100 MB, where the small shapes of step2d.h
+// end, and 128 MB a single pass is long for its size: 176 x 132 x 33^2 99.8,
+// 172 (99.5 MB: 99.1, 81.7).  Past 128 MB two upwind sub-steps take hardly
+// longer than one, and a pass longer than the copy unless its rows end on
+// 64-byte sectors: 212 x 162 x 33^2 149, 169; 559 x 429 x 25^2 560, 632; but
+// 512 x 382 x 17^2 210, 189; 256 x 197 x 33^2 209, 191.
+bool step2d_sub_cut(const lattice_dims& d, int64_t nsub) {
+  const int take = step2d_sub_take(d, nsub);
+  if (take < 2) return false;
+  const size_t elem = d.f64 ? 8 : 4;
+  const double bytes = (double)d.nv * d.nv * d.pitch * elem;
+  if (!d.f64 && bytes > 1e8) {
+    if (!step2d_sub_large(d.nv, d.pitch, d.f64)) return false;
+    StepArgs a = {};
+    a.nx = d.nx;
+    a.pitch = d.pitch;
+    if (!d.koren && take == 2 && d.nv >= 9 && !step2d_aligned(a, elem))
+      return false;
+  }
+  return bytes >= 2.5e5 * d.nv * sqrt((double)d.nv);
 }
 
 hipError_t launch_step2d_sub(const StepArgs& a, hipStream_t s) {
