@@ -198,7 +198,9 @@ hipError_t flow2d(const float* coef, int K, int64_t nx, int64_t ny, double dx,
 // Workspace of flow2d, kept by the handle (at most kFlowWork bytes, or one
 // slice's): slices go through it in chunks.  Under stream capture a
 // stream-ordered allocation that belongs to the graph is used instead, so
-// that a captured call does not depend on the handle's buffer.
+// that a captured call does not depend on the handle's buffer.  The kept one
+// is stream-ordered too: hipMalloc is refused, and ends the capture, while
+// any other stream of the process is being captured.
 constexpr size_t kFlowWork = (size_t)32 << 20;
 template <typename T>
 hipError_t flow2d_call(lattice_t* L, const float* coef, int K, int64_t ns,
@@ -209,7 +211,9 @@ hipError_t flow2d_call(lattice_t* L, const float* coef, int K, int64_t ns,
   chunk = chunk < 1 ? 1 : (chunk > ns ? ns : chunk);
   const size_t need = slice * (size_t)chunk;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  hipError_t e = hipStreamIsCapturing(L->stream, &cap);
+  hipError_t e = hipSuccess;
+  if (L->stream)  // the null stream is never captured
+    e = hipStreamIsCapturing(L->stream, &cap);
   if (e != hipSuccess) return e;
   if (cap != hipStreamCaptureStatusNone) {
     T* work = nullptr;
@@ -220,10 +224,10 @@ hipError_t flow2d_call(lattice_t* L, const float* coef, int K, int64_t ns,
     return e != hipSuccess ? e : f;
   }
   if (L->flow_bytes < need) {
-    if (L->flow_work) (void)hipFree(L->flow_work);  // waits for its users
+    if (L->flow_work) (void)hipFreeAsync(L->flow_work, L->stream);
     L->flow_work = nullptr;
     L->flow_bytes = 0;
-    e = hipMalloc(&L->flow_work, need);
+    e = hipMallocAsync(&L->flow_work, need, L->stream);
     if (e != hipSuccess) {
       L->flow_work = nullptr;
       return e;

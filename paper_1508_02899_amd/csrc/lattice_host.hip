@@ -685,7 +685,8 @@ int lattice_destroy(lattice_t* L) {
   if (L->plane_sums) (void)hipFree(L->plane_sums);
   if (L->red) (void)hipFree(L->red);
   if (L->obs_work) (void)hipFree(L->obs_work);
-  if (L->flow_work) (void)hipFree(L->flow_work);
+  if (L->flow_work && hipFreeAsync(L->flow_work, L->stream) != hipSuccess)
+    (void)hipFree(L->flow_work);
   lat::s1_release(L);
   if (L->host_red) (void)hipHostFree(L->host_red);
   for (hipEvent_t e : L->ev) (void)hipEventDestroy(e);
