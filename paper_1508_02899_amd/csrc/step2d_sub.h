@@ -27,6 +27,12 @@ namespace lat {
 
 constexpr int kSubMax = 4;  // stages of a workgroup
 
+// Whether two Koren sub-steps share a pass past 256 MB (measured per shape:
+// step2d_sub_take).
+constexpr bool sub_koren_past(int nv) {
+  return nv != 5 && nv != 17 && nv != 21;
+}
+
 template <typename T, int NV, int P, bool KOREN, bool INTERIOR, bool FIRST,
           int WPS, bool NT>
 __device__ __forceinline__ void step2d_sub_wave(
@@ -280,8 +286,10 @@ hipError_t launch_step2d_sub_shape(const StepArgs& a, hipStream_t s) {
                        step2d_sector(a, G, sizeof(T)), a.nsub_inline);
   };
   if (BIG && nt) {
+    constexpr bool past = BIG && sub_koren_past(NV);
+    if (a.koren && !past) return hipErrorNotSupported;  // one sub-step a pass
     if (a.koren)
-      go(k_step2d_sub<T, NV, P, true, BIG, WPS>);
+      go(k_step2d_sub<T, NV, P, true, past, WPS>);
     else
       go(k_step2d_sub<T, NV, P, false, BIG, WPS>);
   } else {

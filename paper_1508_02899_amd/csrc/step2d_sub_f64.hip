@@ -44,28 +44,44 @@ bool step2d_sub_large(int nv, int64_t pitch, int f64) {
 //   343 x 394 x 17^2 334, 495, 661 -> 205, 274, 369; 160 x 128 x 33^2 167,
 //   248, 329 -> 137, 161, 190; 400 x 300 x 9^2 53, 79, 103 -> 37, 55, 71,
 //   and with four stages 82, so up to three below 17^2.
+//   Under Koren the stages have to beat the small shapes of step2d.h, which
+//   spread a site's row over more lanes (a pass per sub-step in them against
+//   shared passes, 2 steps): 272 x 199 x 17^2 (3383 wavefronts), 2 sub-steps
+//   1.09 times longer, 192 x 135 x 25^2 (3240) 1.13, 277 x 213 x 13^2 (3834),
+//   3 sub-steps 1.06; but 240 x 182 x 17^2 (2730) 0.89, 176 x 124 x 25^2
+//   (2728) 0.91: up to 3000 while the state is in their range (100 MB). At
+//   21^2 a lane holds six cells, and the stages lose from 1140 wavefronts on:
+//   160 x 114, 2 and 3 sub-steps 1.12 and 1.19; 224 x 161 256 us a step with
+//   a pass per sub-step before those shapes, 156 with them, 235 shared; at
+//   744 wavefronts 0.68, 0.87, and past 3000 again 0.72.
 //   Large lattices, bound by memory: FP32 only (FP64 Koren is bound by its
 //   arithmetic).  65^2, 256^2 sites: 834, 1238, 1646 -> 737, 1272, 1359;
 //   33^2, 512^2 sites: 835, 1249, 1665 -> 737, 1474, 1632; upwind 823, 1238,
 //   1649 -> 559, 1008, 1097.  Three stages of two wavefronts leave two of the
 //   four SIMDs with half the work, and four are no better than two twice
 //   under Koren below 65^2.  In one wavefront per stage: 400 x 300 x 17^2
-//   151, 224, 301 -> 101, 157, 227, upwind 136, 204, 274 -> 76, 102, 132;
-//   512^2 x 17^2 232 -> 246 and 512^2 x 21^2 381 -> 416 under Koren, where
-//   the state is past 256 MB.
+//   151, 224, 301 -> 101, 157, 227, upwind 136, 204, 274 -> 76, 102, 132.
+//   Past 256 MB under Koren (sub_koren_past), 2 sub-steps: 512^2 x 17^2 232 ->
+//   246, 512^2 x 21^2 381 -> 416, 2432 x 1860 x 5^2 (452 MB) 350 -> 388, 851
+//   MB 1.04 times; but 9^2 0.59 to 0.76 times at 300 to 1100 MB, 13^2 0.83 to
+//   1.03.
 int step2d_sub_take(const lattice_dims& d, int64_t left) {
   const int P = sub_parts(d.nv, d.f64);
   if (P == 0 || left < 2) return 1;
   int64_t most;
+  const int64_t bytes = (int64_t)d.nv * d.nv * d.pitch * (d.f64 ? 8 : 4);
   if (step2d_sub_large(d.nv, d.pitch, d.f64)) {
-    const bool past = (int64_t)d.nv * d.nv * d.pitch * 4 > (256ll << 20);
     most = !d.koren || d.nv >= 65 ? kSubMax
-           : past && (d.nv == 17 || d.nv == 21) ? 1 : 2;
+           : bytes > (256ll << 20) && !sub_koren_past(d.nv) ? 1 : 2;
     if (d.nv >= 25) return left >= 4 && most == 4 ? 4 : 2;
   } else {
     const int64_t S = 64 / P;
     const int64_t waves = (d.nx + S - 1) / S * d.ny;
     most = (d.f64 ? 2500 : 8000) / waves;
+    if (d.koren && !d.f64 && bytes <= 100000000) {
+      if (waves > 3000 && d.nv != 21) most = 1;
+      if (waves > 800 && waves <= 3000 && d.nv == 21) most = 1;
+    }
     if (d.f64 && !d.koren && most < kSubMax) most = d.nv >= 17 ? kSubMax : 3;
     if (most > kSubMax) most = kSubMax;
   }

@@ -803,3 +803,29 @@ def test_2d_odd_number_of_passes(nv, dtype, nx, ny, scheme, cut):
             step_noalloc(spec, g, ud, *args, nsteps)
             assert torch.equal(f, g)
         del f, g, start
+
+
+@pytest.mark.parametrize("nv,nx,ny,scheme,nsub,passes", [
+    (21, 228, 174, "koren", 3, 3), (21, 160, 114, "koren", 2, 2),
+    (21, 228, 174, "upwind", 3, 1), (21, 128, 93, "koren", 3, 1),
+    (17, 272, 199, "koren", 2, 2), (17, 240, 182, "koren", 2, 1),
+    (25, 192, 135, "koren", 4, 4), (5, 1984, 1519, "koren", 2, 2),
+    (5, 1408, 1074, "koren", 2, 1), (9, 1104, 843, "koren", 2, 1)])
+def test_2d_sub_steps_share_a_pass_only_where_it_is_shorter(nv, nx, ny, scheme,
+                                                           nsub, passes):
+    """Passes of a step on lattices where a pass per sub-step is the faster
+    form (Koren: 21^2 from 800 wavefronts, others from 3000, 5^2 past 256
+    MB), and on their neighbours where it is not."""
+    import torch
+    from paper_1508_02899_amd import Lattice, LatticeSpec
+    spec = LatticeSpec(dim=2, nx=nx, ny=ny, nv=nv, dx=0.1, scheme=scheme,
+                       nsub=nsub)
+    dv = 3.0 / ((nv - 1) // 2)
+    dt = 0.1 / dv
+    f = torch.ones(spec.state_shape, device="cuda")
+    u = torch.zeros(spec.u_shape(1), device="cuda")
+    with Lattice(spec) as lat:
+        lat.profile(True)
+        lat.step(f, u, dt / (nsub * dv) * 15, 1e-6, dt, 2)
+        lat.sync()
+        assert lat.profile_read()[1] == 2 * passes
