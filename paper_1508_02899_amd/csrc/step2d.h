@@ -662,10 +662,24 @@ inline int64_t step2d_waves(const StepArgs& a, int P) {
 //   P (to 2400): 150 x 130 x 33^2 78.7 -> 38.4, 150 x 130 x 21^2 40.4 -> 20.6,
 //       192 x 192 x 17^2 FP64 (2304) 44.4 -> 41.0; at 2560, 300 x 256 x 17^2
 //       upwind 31.5 -> 33.6
+// Upwind rows are short chains: from 33 velocities on 2 P loses sooner, where
+// the default shape's workgroups run in one round (two steps with a copy, us,
+// default -> 2 P): 33^2 at 1998 wavefronts, 144 x 111, 65.4 -> 59.5, at 2324,
+// 112 x 166, 67.1 -> 72.5, 267 x 76 70.0 -> 81.0, but 150 x 130 (260 workgroups)
+// 119 -> 79; 65^2 at 1280, 80 x 64, 122 -> 116, at 1340, 77 x 67, 125 -> 137;
+// FP64 33^2 at 1520, 64 x 95, 50.1 -> 49.6, at 1736, 112 x 62, 50.7 -> 53.1,
+// 80 x 121 68.2 -> 73.2.
 template <typename T, int NV, int P>
 hipError_t launch_step2d_nv(const StepArgs& a, hipStream_t s) {
-  const bool small = (uint64_t)NV * NV * (uint64_t)a.pitch * sizeof(T) <=
-                     100000000ull;
+  bool small = (uint64_t)NV * NV * (uint64_t)a.pitch * sizeof(T) <=
+               100000000ull;
+  if constexpr (NV >= 33) {
+    constexpr int G = OutStage<T, NV, P, step2d_wgw<T, NV, P>()>::G;
+    const int64_t most = sizeof(T) == 8 ? 1550 : (NV >= 65 ? 1300 : 2000);
+    if (!a.koren && step2d_waves(a, 2 * P) > most &&
+        (sizeof(T) == 8 || (a.nx + G - 1) / G * a.ny <= 256))
+      small = false;
+  }
   if constexpr (NV >= 7 && NV < 65 && (NV - 1) % (4 * P) == 0 &&
                 (NV - 1) / (4 * P) >= 2 && sizeof(T) == 4) {
     if (small && step2d_waves(a, 4 * P) <= 1100)

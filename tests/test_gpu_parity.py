@@ -829,3 +829,13 @@ def test_2d_sub_steps_share_a_pass_only_where_it_is_shorter(nv, nx, ny, scheme,
         lat.step(f, u, dt / (nsub * dv) * 15, 1e-6, dt, 2)
         lat.sync()
         assert lat.profile_read()[1] == 2 * passes
+
+
+@pytest.mark.parametrize("nv,dtype,nx,ny", [
+    (33, "f32", 109, 141), (33, "f32", 113, 141), (33, "f32", 150, 130),
+    (65, "f32", 77, 65), (65, "f32", 77, 66), (33, "f64", 111, 55),
+    (33, "f64", 111, 56)])
+def test_2d_upwind_small_lattices_of_many_velocities(nv, dtype, nx, ny):
+    """Both sides of the line at which upwind lattices of 33^2 and 65^2 go
+    back to the default shape."""
+    test_2d_small_lattice_shapes(nv, dtype, nx, ny, "upwind")
