@@ -184,30 +184,68 @@ __global__ __launch_bounds__(64 * NW) void k_density(
   }
 }
 
+// A lane per site, walking all the planes, U loads in flight.
+template <typename T, int U>
+__global__ __launch_bounds__(kBlock) void k_density_lane(
+    const T* __restrict__ f, int64_t sites, int64_t pitch, int nplanes,
+    double dvd, double* __restrict__ rho) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= sites) return;
+  const T* p = f + i;
+  double acc = 0.0;
+#pragma unroll U
+  for (int j = 0; j < nplanes; ++j, p += pitch) acc += (double)*p;
+  rho[i] = dvd * acc;
+}
+
+// Many sites fill the chip with a lane per site, and there the wavefronts of
+// a workgroup that read several planes at once gain nothing (us, FP32 unless
+// said; "wide" is 16-byte loads by 4 or 16 wavefronts):
+//   sites that no 16-byte load divides: 1048577 x 3, 17, 65, 81 planes 6.2,
+//   19.3, 87.8, 120.7 by 4 or 16 wavefronts, 4.4, 14.5, 50.2, 73.2 by a lane
+//   with two loads in flight; 262145 x 289, 1089 62.7, 240, 80, 323 with two
+//   loads and 50.9, 193 with eight;
+//   planes that all start on the same memory channels (a multiple of 64 KiB
+//   apart): 524288 x 33, 65 planes wide 18.4, 36.3, two wavefronts with
+//   4-byte loads 11.7, 21.1, but 1048576 x 9 9.4, 11.4; FP64 262144 x 33, 65,
+//   81 wide 17.8, 36.5, 37.9, a lane 11.8, 20.8, 25.3, 524288 x 9, 289 8.4, 230,
+//   7.3, 203, but 262144 x 17 5.5, 7.4 and 4194304 x 33 196, 207;
+//   elsewhere 800000 x 33, 65 wide 18.3, 31.7, two wavefronts 16.9, 32.3.
 template <typename T>
 void density_go(const T* f, int64_t sites, int64_t pitch, int nplanes,
                 double dvd, double* rho, hipStream_t s) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  const bool aligned = sites % VEC == 0 && pitch % VEC == 0 &&
+                       ((uintptr_t)f & 15) == 0;
   // 16-byte loads once they still leave two workgroups per compute unit,
   // and only where every plane and the sites allow the alignment
-  constexpr int VEC = 16 / (int)sizeof(T);
-  const bool wide = sites >= (int64_t)64 * VEC * 512 && sites % VEC == 0 &&
-                    pitch % VEC == 0 && ((uintptr_t)f & 15) == 0;
-  auto go = [&](auto kernel, int vec, int nw) {
-    const int64_t g = (sites + 64 * vec - 1) / (64 * vec);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(64 * nw), 0, s, f,
+  const bool wide = sites >= (int64_t)64 * VEC * 512 && aligned;
+  auto go = [&](auto kernel, int per, int threads) {
+    const int64_t g = (sites + per - 1) / per;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(threads), 0, s, f,
                        sites, pitch, nplanes, dvd, rho);
   };
+  if (sites >= 262144 && !aligned)
+    return nplanes < 96 ? go(k_density_lane<T, 2>, kBlock, kBlock)
+                        : go(k_density_lane<T, 8>, kBlock, kBlock);
+  if (sites >= 262144 && (uint64_t)pitch * sizeof(T) % 65536 == 0) {
+    if (sizeof(T) == 4 && nplanes >= 17 && nplanes < 128)
+      return go(k_density<T, 1, 2>, 64, 128);
+    if (sizeof(T) == 8 && sites <= (1 << 21) &&
+        (sites >= 524288 || (nplanes >= 32 && nplanes < 128)))
+      return go(k_density_lane<T, 1>, kBlock, kBlock);
+  }
   // 16 wavefronts where each still has a run of planes to add
   if (nplanes >= 64) {
     if (wide)
-      go(k_density<T, VEC, 16>, VEC, 16);
+      go(k_density<T, VEC, 16>, 64 * VEC, 64 * 16);
     else
-      go(k_density<T, 1, 16>, 1, 16);
+      go(k_density<T, 1, 16>, 64, 64 * 16);
   } else {
     if (wide)
-      go(k_density<T, VEC, 4>, VEC, 4);
+      go(k_density<T, VEC, 4>, 64 * VEC, 64 * 4);
     else
-      go(k_density<T, 1, 4>, 1, 4);
+      go(k_density<T, 1, 4>, 64, 64 * 4);
   }
 }
 

@@ -100,3 +100,19 @@ def test_density_sums_every_plane_once(dim, nx, ny, nv, dtype, pad):
     assert float(((got - want) / want).abs().max()) <= tol
     assert torch.equal(got, lat.density(f, dt))
     lat.close()
+
+
+@pytest.mark.parametrize("dim,nx,ny,nv,dtype,pad", [
+    # a lane per site where no wide load fits, two and eight loads in flight
+    (1, 262143, 1, 17, "f32", 0), (1, 262145, 1, 17, "f32", 0),
+    (1, 262145, 1, 129, "f32", 0), (2, 641, 411, 9, "f64", 0),
+    (2, 641, 411, 11, "f32", 1),
+    # planes 64 KiB apart: two wavefronts (FP32), a lane (FP64), and beside
+    (1, 262144, 1, 17, "f32", 0), (2, 512, 512, 9, "f32", 0),
+    (2, 512, 512, 9, "f32", 64), (1, 262144, 1, 9, "f32", 0),
+    (2, 512, 512, 9, "f64", 0), (1, 262144, 1, 17, "f64", 0),
+    (1, 524288, 1, 3, "f64", 0), (1, 1 << 21, 1, 3, "f64", 0),
+    (1, (1 << 21) + 8192, 1, 3, "f64", 0)])
+def test_density_of_many_sites(dim, nx, ny, nv, dtype, pad):
+    """The forms for many sites on both sides of each line."""
+    test_density_sums_every_plane_once(dim, nx, ny, nv, dtype, pad)
