@@ -44,7 +44,7 @@ struct lattice {
 };
 
 namespace lat {
-constexpr int kHostRed = 64;  // doubles read back through pinned memory
+constexpr int kHostRed = 2048;  // doubles read back through pinned memory
 // frees what lattice_s1 keeps (s1.hip)
 void s1_release(lattice_t* L);
 // learned correction pass (coarse_host.hip)

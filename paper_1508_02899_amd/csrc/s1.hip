@@ -59,11 +59,20 @@ __global__ __launch_bounds__(kS1Block) void k_s1_dist(int nv, T* __restrict__ D)
 
 constexpr int kS1Sites = 2;  // sites per thread of k_s1_num
 
-// A set of up to NQ separations: along x (dx sites, already mod nx) or along
-// y (dy, mod ny), one of the two being zero.
-template <int NQ>
+// The separations of one launch, r mod nx (mod ny where they are along y):
+// with naxes = 2, even ones along x and odd ones along y.  Few of them travel
+// as kernel arguments, more in device memory (at; zeros past the last one).  A
+// launch takes them in sets of NQ, set blockIdx.y: a launch per set made many
+// separations of a short lattice a matter of launches (4096 x 17, 40 of them:
+// one launch for all 42 us, one per 16 86, one for all again 37; 600 of
+// them 72, 565, 75).
+constexpr int kS1Few = 48;
 struct S1Seps {
-  int32_t dx[NQ], dy[NQ];
+  const int32_t* at;
+  int32_t r[kS1Few];
+  __device__ __forceinline__ uint32_t get(int g) const {
+    return (uint32_t)(at ? at[g] : r[g]);
+  }
 };
 
 // Partial sums of sum_J f_J(x) h_J(x') over a chunk of sites and a group of
@@ -72,12 +81,12 @@ struct S1Seps {
 // same few planes, xcd_remap).  Bound by the h loads: 12 separations of
 // 256^2 x 17^2 take 71 us, where a pass per separation that also summed
 // rho(x) and rho(x') took 197 us.
-// partial[q nblocks + block].
+// partial[(set NQ + q) nblocks + block].
 template <typename T, int NQ>
 __global__ __launch_bounds__(kS1Block) void k_s1_num(
     const T* __restrict__ f, int64_t fpitch, const T* __restrict__ h, int nx,
-    int ny, int nplanes, int nchunks, int per, S1Seps<NQ> sep,
-    double* __restrict__ partial) {
+    int ny, int nplanes, int nchunks, int per, S1Seps sep,
+    int naxes, double* __restrict__ partial) {
   __shared__ double sh[NQ][kS1Block / 64];
   const int sites = nx * ny;
   const int blk = xcd_remap((int)blockIdx.x, (int)gridDim.x);
@@ -94,8 +103,11 @@ __global__ __launch_bounds__(kS1Block) void k_s1_num(
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       // unsigned: both below 2^31, so the sums stay below 2^32
-      uint32_t xs = (uint32_t)x + (uint32_t)sep.dx[q];
-      uint32_t ys = (uint32_t)y + (uint32_t)sep.dy[q];
+      const int g = (int)blockIdx.y * NQ + q;
+      const uint32_t r = sep.get(g);
+      const bool along_y = naxes == 2 && (g & 1);
+      uint32_t xs = (uint32_t)x + (along_y ? 0u : r);
+      uint32_t ys = (uint32_t)y + (along_y ? r : 0u);
       if (xs >= (uint32_t)nx) xs -= (uint32_t)nx;
       if (ys >= (uint32_t)ny) ys -= (uint32_t)ny;
       to[e][q] = (int)(ys * (uint32_t)nx + xs);
@@ -129,7 +141,7 @@ __global__ __launch_bounds__(kS1Block) void k_s1_num(
   __syncthreads();
   if ((int)threadIdx.x < NQ) {
     const double* p = sh[threadIdx.x];
-    partial[(size_t)threadIdx.x * gridDim.x + blk] =
+    partial[((size_t)blockIdx.y * NQ + threadIdx.x) * gridDim.x + blk] =
         (p[0] + p[1]) + (p[2] + p[3]);
   }
 }
@@ -144,13 +156,15 @@ __device__ double block_sum(double a, double* sh) {
 
 // Partial sums of rho(x) rho(x') over a chunk of sites of one separation.
 constexpr int kDenSites = 4;  // sites per thread
-template <int NQ>
 __global__ __launch_bounds__(kS1Block) void k_s1_den(
-    const double* __restrict__ rho, int nx, int ny, S1Seps<NQ> sep,
+    const double* __restrict__ rho, int nx, int ny, S1Seps sep, int naxes,
     double* __restrict__ partial) {
   __shared__ double sh[kS1Block / 64];
   const int64_t sites = (int64_t)nx * ny;
   const int q = blockIdx.y;
+  const bool along_y = naxes == 2 && (q & 1);
+  const uint32_t r = sep.get(q);
+  const uint32_t dx = along_y ? 0u : r, dy = along_y ? r : 0u;
   double acc = 0.0;
 #pragma unroll 4
   for (int e = 0; e < kDenSites; ++e) {
@@ -158,8 +172,8 @@ __global__ __launch_bounds__(kS1Block) void k_s1_den(
         ((int64_t)blockIdx.x * kDenSites + e) * kS1Block + threadIdx.x;
     if (i < sites) {
       const int y = (int)(i / nx), x = (int)(i - (int64_t)y * nx);
-      uint32_t xs = (uint32_t)x + (uint32_t)sep.dx[q];
-      uint32_t ys = (uint32_t)y + (uint32_t)sep.dy[q];
+      uint32_t xs = (uint32_t)x + dx;
+      uint32_t ys = (uint32_t)y + dy;
       if (xs >= (uint32_t)nx) xs -= (uint32_t)nx;
       if (ys >= (uint32_t)ny) ys -= (uint32_t)ny;
       acc += rho[i] * rho[(size_t)ys * nx + xs];
@@ -188,73 +202,87 @@ __global__ __launch_bounds__(kS1Block) void k_s1_final(
   }
 }
 
-// Workgroups of k_s1_num: chunks of sites, times groups of `per` planes so
-// that a few thousand workgroups run whatever the sizes are.
-struct S1Grid {
+// How `total` separations are cut into sets of nq (4, 8, 12 or 16, the fewest
+// loads: an f per set and an h per slot, the unused ones included), and the
+// workgroups of k_s1_num: chunks of sites, times groups of `per` planes so
+// that a few thousand run in all sets together, whatever the sizes are (the
+// order of a separation's additions depends on the sizes and on `total`).
+struct S1Cut {
+  int nq, sets;  // sets of a launch: the partial sums stay below 16 MB
   int nchunks, per, groups;
   int64_t nden;  // workgroups per separation of k_s1_den
+  size_t npart;  // doubles of partial sums
 };
 
-S1Grid s1_grid(int64_t sites, int nplanes) {
-  S1Grid g;
-  g.nchunks = (int)((sites + kS1Block * kS1Sites - 1) / (kS1Block * kS1Sites));
-  int groups = (2048 + g.nchunks - 1) / g.nchunks;
+S1Cut s1_cut(int total, int64_t sites, int nplanes) {
+  S1Cut c = {};
+  int64_t best = -1;
+  for (int nq = 16; nq >= 4; nq -= 4) {
+    const int64_t cost = (int64_t)((total + nq - 1) / nq) * (nq + 2);
+    if (best < 0 || cost < best) {
+      best = cost;
+      c.nq = nq;
+    }
+  }
+  c.sets = (total + c.nq - 1) / c.nq;
+  c.nchunks = (int)((sites + kS1Block * kS1Sites - 1) / (kS1Block * kS1Sites));
+  const int64_t blocks = (int64_t)c.nchunks * c.sets;
+  int64_t groups = (2048 + blocks - 1) / blocks;
   groups = groups < 1 ? 1 : (groups > nplanes ? nplanes : groups);
-  g.per = (nplanes + groups - 1) / groups;
-  g.groups = (nplanes + g.per - 1) / g.per;
-  g.nden = (sites + kS1Block * kDenSites - 1) / (kS1Block * kDenSites);
-  return g;
+  c.per = (int)((nplanes + groups - 1) / groups);
+  c.groups = (nplanes + c.per - 1) / c.per;
+  c.nden = (sites + kS1Block * kDenSites - 1) / (kS1Block * kDenSites);
+  const size_t set =
+      (size_t)c.nq * ((size_t)c.nchunks * c.groups + (size_t)c.nden);
+  while (c.sets > 1 && (size_t)c.sets * set > ((size_t)1 << 21))
+    c.sets = (c.sets + 1) / 2;
+  c.npart = (size_t)c.sets * set;
+  return c;
 }
 
-// Separations first .. first + nq - 1 (in the order r[0] along x, r[0] along
-// y, r[1] along x, ...) into sums[2 q], q < nq; nq <= NQ.
+// Separations first .. first + n - 1 (r[0] along x, r[0] along y, r[1] along
+// x, ..., each modulo the lattice; first is a multiple of 4) into
+// sums[2 first ..].
 template <typename T, int NQ>
 hipError_t correlate(const T* f, int64_t fpitch, const T* h,
                      const double* rho, int64_t nx, int64_t ny, int nplanes,
-                     const int32_t* r, int naxes, int first, int nq,
-                     const S1Grid& g, double* partial, double* sums,
+                     const S1Seps& seps, int naxes, int first, int n,
+                     const S1Cut& c, double* partial, double* sums,
                      hipStream_t st) {
-  S1Seps<NQ> sep = {};
-  for (int q = 0; q < nq; ++q) {
-    const int k = (first + q) / naxes, axis = (first + q) - k * naxes;
-    if (axis == 0)
-      sep.dx[q] = (int32_t)(r[k] % nx);
-    else
-      sep.dy[q] = (int32_t)(r[k] % ny);
-  }
-  const int nb = g.nchunks * g.groups;
-  double* const den = partial + (size_t)NQ * nb;
-  hipLaunchKernelGGL((k_s1_num<T, NQ>), dim3(nb), dim3(kS1Block), 0, st, f,
-                     fpitch, h, (int)nx, (int)ny, nplanes, g.nchunks, g.per,
-                     sep, partial);
-  hipLaunchKernelGGL((k_s1_den<NQ>), dim3((unsigned)g.nden, nq),
-                     dim3(kS1Block), 0, st, rho, (int)nx, (int)ny, sep, den);
-  hipLaunchKernelGGL(k_s1_final, dim3(nq), dim3(kS1Block), 0, st, partial, nb,
-                     den, (int)g.nden, sums + 2 * first);
+  S1Seps sep = seps;
+  if (sep.at) sep.at += first;
+  const int nb = c.nchunks * c.groups;
+  const int sets = (n + NQ - 1) / NQ;
+  double* const den = partial + (size_t)sets * NQ * nb;
+  hipLaunchKernelGGL((k_s1_num<T, NQ>), dim3(nb, sets), dim3(kS1Block), 0, st,
+                     f, fpitch, h, (int)nx, (int)ny, nplanes, c.nchunks, c.per,
+                     sep, naxes, partial);
+  hipLaunchKernelGGL(k_s1_den, dim3((unsigned)c.nden, n), dim3(kS1Block), 0,
+                     st, rho, (int)nx, (int)ny, sep, naxes, den);
+  hipLaunchKernelGGL(k_s1_final, dim3(n), dim3(kS1Block), 0, st, partial, nb,
+                     den, (int)c.nden, sums + 2 * first);
   return hipGetLastError();
 }
-
-constexpr int kS1MaxQ = 16;
 
 template <typename T>
 hipError_t correlate_all(const T* f, int64_t fpitch, const T* h,
                          const double* rho, int64_t nx, int64_t ny,
-                         int nplanes, const int32_t* r, int naxes, int total,
-                         const S1Grid& g, double* partial, double* sums,
+                         int nplanes, const S1Seps& seps, int naxes, int total,
+                         const S1Cut& c, double* partial, double* sums,
                          hipStream_t st) {
-  for (int first = 0; first < total; first += kS1MaxQ) {
-    const int nq = total - first < kS1MaxQ ? total - first : kS1MaxQ;
-    auto go = [&](auto n) {
-      return correlate<T, decltype(n)::value>(f, fpitch, h, rho, nx, ny,
-                                              nplanes, r, naxes, first, nq, g,
-                                              partial, sums, st);
+  const int most = c.sets * c.nq;
+  for (int first = 0; first < total; first += most) {
+    const int n = total - first < most ? total - first : most;
+    auto go = [&](auto nq) {
+      return correlate<T, decltype(nq)::value>(f, fpitch, h, rho, nx, ny,
+                                               nplanes, seps, naxes, first, n,
+                                               c, partial, sums, st);
     };
-    // unused slots of a set load h like the used ones: the smallest set
     const hipError_t e =
-        nq <= 4 ? go(std::integral_constant<int, 4>())
-        : nq <= 8 ? go(std::integral_constant<int, 8>())
-        : nq <= 12 ? go(std::integral_constant<int, 12>())
-                   : go(std::integral_constant<int, kS1MaxQ>());
+        c.nq == 4 ? go(std::integral_constant<int, 4>())
+        : c.nq == 8 ? go(std::integral_constant<int, 8>())
+        : c.nq == 12 ? go(std::integral_constant<int, 12>())
+                     : go(std::integral_constant<int, 16>());
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -279,12 +307,14 @@ extern "C" int lattice_s1(lattice_t* L, const void* f, double dt, int32_t nr,
   const int64_t np = L->nplanes;
   const int total = nr * naxes;
   hipStream_t st = L->stream;
-  // workspace: rho, the partial sums of one set of separations, the sums
-  const lat::S1Grid g = lat::s1_grid(sites, (int)np);
-  const size_t npart =
-      (size_t)lat::kS1MaxQ * ((size_t)g.nchunks * g.groups + (size_t)g.nden);
-  const size_t need = sizeof(double) * ((size_t)sites + npart +
-                                        2 * (size_t)total);
+  // workspace: rho, the partial sums of one launch's separations, the sums,
+  // the separations (when they do not go as kernel arguments)
+  const lat::S1Cut cut = lat::s1_cut(total, sites, (int)np);
+  const int slots = (total + cut.nq - 1) / cut.nq * cut.nq;
+  const bool few = slots <= lat::kS1Few;
+  const size_t need = sizeof(double) * ((size_t)sites + cut.npart +
+                                        2 * (size_t)total) +
+                      sizeof(int32_t) * (few ? 0 : (size_t)slots);
   if (L->s1_bytes < need) {
     if (L->s1_work) (void)hipFree(L->s1_work);
     L->s1_work = nullptr;
@@ -297,7 +327,8 @@ extern "C" int lattice_s1(lattice_t* L, const void* f, double dt, int32_t nr,
   }
   double* const rho = L->s1_work;
   double* const partial = rho + sites;
-  double* const sums = partial + npart;
+  double* const sums = partial + cut.npart;
+  int32_t* const at = few ? nullptr : (int32_t*)(sums + 2 * (size_t)total);
   void* const h = L->scratch;  // at least the cells of a state
   int rc = LATTICE_OK;
   hipError_t e = hipSuccess;
@@ -366,16 +397,26 @@ extern "C" int lattice_s1(lattice_t* L, const void* f, double dt, int32_t nr,
     }
     if (bs != rocblas_status_success) rc = LATTICE_EHIP;
   }
+  lat::S1Seps seps = {at, {}};
+  int32_t* const rs = few ? seps.r : new (std::nothrow) int32_t[slots];
+  if (!rs) rc = LATTICE_ENOMEM;
+  for (int q = 0; rs && q < slots; ++q)
+    rs[q] = q >= total ? 0
+                       : (int32_t)(r[q / naxes] %
+                                   (q % naxes == 0 ? d.nx : d.ny));
+  if (rc == LATTICE_OK && e == hipSuccess && !few)
+    e = hipMemcpyAsync(at, rs, sizeof(int32_t) * slots, hipMemcpyHostToDevice,
+                       st);
   if (rc == LATTICE_OK && e == hipSuccess)
     e = lat::launch_density(f, sites, L->pitch, (int)np, f64, 1.0, rho, st);
   if (rc == LATTICE_OK && e == hipSuccess) {
     const int64_t ny = d.dim == 2 ? d.ny : 1;
     e = f64 ? lat::correlate_all((const double*)f, L->pitch, (const double*)h,
-                                 rho, d.nx, ny, (int)np, r, naxes, total, g,
-                                 partial, sums, st)
+                                 rho, d.nx, ny, (int)np, seps, naxes, total,
+                                 cut, partial, sums, st)
             : lat::correlate_all((const float*)f, L->pitch, (const float*)h,
-                                 rho, d.nx, ny, (int)np, r, naxes, total, g,
-                                 partial, sums, st);
+                                 rho, d.nx, ny, (int)np, seps, naxes, total,
+                                 cut, partial, sums, st);
   }
   // pinned memory for the usual few separations
   double* hs = 2 * total <= lat::kHostRed ? L->host_red
@@ -403,6 +444,7 @@ extern "C" int lattice_s1(lattice_t* L, const void* f, double dt, int32_t nr,
     }
   }
   if (hs != L->host_red) delete[] hs;
+  if (!few) delete[] rs;
   return rc;
 }
 

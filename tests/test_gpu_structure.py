@@ -77,3 +77,14 @@ def test_s1_sets_of_separations(dim, nx, ny, nv, dtype, pad, nr):
     err = np.max(np.abs(got - want) / np.abs(want))
     say(f"  max rel err {err:.2e}")
     assert err < (1e-5 if dtype == "f32" else 1e-12)
+
+
+@pytest.mark.parametrize("dim,nx,ny,nv,dtype,pad,nr", [
+    (1, 257, 1, 5, "f32", 0, 17), (1, 300, 1, 3, "f64", 0, 40),
+    (1, 64, 1, 3, "f64", 0, 48), (1, 64, 1, 3, "f64", 0, 49),
+    (1, 40, 1, 3, "f64", 0, 1000), (2, 17, 12, 3, "f64", 5, 70),
+    (2, 12, 9, 3, "f32", 0, 600)])
+def test_s1_many_sets_of_separations_in_a_launch(dim, nx, ny, nv, dtype, pad,
+                                                 nr):
+    """Several sets a launch, the last one not full, and several launches."""
+    test_s1_sets_of_separations(dim, nx, ny, nv, dtype, pad, nr)
