@@ -1131,6 +1131,7 @@ void k_mlp_correct17(
       if (use) queue[w][nq + before] = (uint16_t)(fbase + k);
       nq += __popcll(b);
     }
+    if (nq == 0) continue;  // uniform: the site stays as it is
     for (int i = l; i < NV * (NV + 1); i += 64) {
       (&gx[w][0][0])[i] = 0.f;
       (&gy[w][0][0])[i] = 0.f;
@@ -1338,8 +1339,14 @@ hipError_t launch_mlp_correct(const CoarseGeom& g, const float* params,
   // 8e-3, tiles of 32, 16, 8, 4 sites: 53 x 137 sites 318, 234, 210, 199;
   // 128^2 398, 379, 347, 343; 180^2 638, 598, 592, 591; 240^2 1017, 938, 911,
   // 940; 256^2 1057, 1020, 1047, 1059; 384^2 2166, 2168, 2208, 2291; 512^2
-  // 3774, 3819, 3858, 4094).
-  if (S <= 28000)
+  // 3774, 3819, 3858, 4094).  A cell lies in the stencils of ten faces at
+  // most, so a threshold of 0.1 leaves a site at most 100 of its 544 faces and
+  // 0.3 a third of that: then the weights are the larger share (two steps of
+  // 160^2, tiles of 32 and 4: threshold 0.05 351, 284 us; 0.1 218, 244; 0.3 146,
+  // 215; 53 x 37 sites, which leave compute units idle, 0.1 108, 58).
+  if (g.line_eps >= 0.1f && S > 8000)
+    go(k_mlp_correct17<32>, 32);
+  else if (S <= 28000)
     go(k_mlp_correct17<4>, 4);
   else if (S <= 60000)
     go(k_mlp_correct17<8>, 8);

@@ -417,3 +417,59 @@ def test_correction_tiles_of_every_size(nx, ny, kx, ky):
         size = rel_l2(want, c)
         assert rel_l2(got[:, y, x], want) < 2e-3 * max(1.0, size / 1e-2)
     m.close()
+
+
+@pytest.mark.parametrize("eps,rep", [(0.0999, 23), (0.1, 22), (0.1, 23),
+                                     (0.2, 23)])
+def test_correction_at_thresholds_that_leave_few_faces(eps, rep):
+    """Thresholds and sizes on both sides of the line at which a lattice takes
+    tiles of 32 sites because few faces pass: 4 x 4 sites, which streaming by
+    multiples of 4 leaves in place, repeated rep x rep times, some spread too
+    evenly for any face (left as they are), the others in a few cells.  One
+    period against the oracle, the rest bit for bit."""
+    import torch
+    from oracle import coarse as C
+    from paper_1508_02899_amd import Lattice, LatticeSpec, Mlp
+    rng = np.random.default_rng(7)
+    nv, nx, ny = 17, 4, 4
+    f0, _, u = _coarse_case(rng, nx, ny)
+    j = np.arange(nv) - 8
+    f0[:] = (np.exp(-0.5 * (j[:, None] ** 2 + (j[None, :] - 2) ** 2)).reshape(
+        nv * nv, 1, 1) + 1e-4) * (0.5 + rng.random(f0.shape))
+    f0[:, ::2, ::3] = 1.0 + 0.01 * rng.random(f0[:, ::2, ::3].shape)
+    f0 = f0.astype(np.float32)
+    dx, dt, tau_p, St = 2 * math.pi / 40, 0.05, 40.0, 1.5
+    P = _params(rng, 0.3)
+    m = Mlp()
+    m.set_params(_pack(P))
+    ud = torch.from_numpy(u[:1]).cuda().repeat(1, 1, rep, rep).contiguous()
+    out = []
+    for attach in (False, True):
+        f = torch.from_numpy(f0).cuda().repeat(1, rep, rep).contiguous()
+        with Lattice(LatticeSpec(dim=2, nx=rep * nx, ny=rep * ny, nv=nv,
+                                 dx=dx, vstride=4)) as lat:
+            if attach:
+                m.attach(lat, St, eps)
+            lat.step(f, ud, tau_p, 0.0, dt, 1)
+            lat.sync()
+        assert torch.equal(f, f[:, :ny, :nx].repeat(1, rep, rep))
+        out.append(f[:, :ny, :nx].cpu().numpy())
+    mid, got = out[0].astype(np.float64), out[1]
+    Pq = _unpack(_pack(P))
+    kept = 0
+    for y in range(ny):
+        for x in range(nx):
+            c = mid[:, y, x]
+            Xo, ms, sg = C.face_features(c, nv, float(u[0, 0, y, x]),
+                                         float(u[0, 1, y, x]), 4 * dx / dt,
+                                         dt, tau_p, St)
+            yo, _ = C.forward(Pq, Xo)
+            want = C.corrected_site(c, nv, yo, ms, sg, line_eps=eps)
+            size = rel_l2(want, c)
+            assert rel_l2(got[:, y, x], want) < 2e-3 * max(1.0, size / 1e-2)
+            if size == 0.0:
+                kept += 1
+                assert np.array_equal(got[:, y, x], out[0][:, y, x])
+    say(f"  {kept} of {nx * ny} sites without faces")
+    assert 0 < kept < nx * ny
+    m.close()
