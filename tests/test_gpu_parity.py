@@ -839,3 +839,42 @@ def test_2d_upwind_small_lattices_of_many_velocities(nv, dtype, nx, ny):
     """Both sides of the line at which upwind lattices of 33^2 and 65^2 go
     back to the default shape."""
     test_2d_small_lattice_shapes(nv, dtype, nx, ny, "upwind")
+
+
+@pytest.mark.parametrize("nx,nv,dtype,nsub,nsteps", [
+    # both sides of every line of the rule (sites by weight of the update),
+    # with step counts that need an odd number of launches, spread unevenly
+    (65536, 9, "f32", 1, 33), (65537, 9, "f32", 1, 5),
+    (32768, 33, "f32", 1, 9), (32768, 17, "f64", 1, 19),
+    (32769, 17, "f64", 1, 3), (32768, 13, "f32", 3, 23),
+    (32769, 13, "f32", 3, 3), (16384, 5, "f32", 8, 33),
+    (16385, 5, "f32", 8, 3), (8192, 5, "f64", 5, 33), (8193, 5, "f64", 5, 3),
+    (200, 9, "f64", 6, 3), (8192, 33, "f64", 1, 9)])
+def test_1d_several_steps_at_the_ends_of_their_ranges(nx, nv, dtype, nsub,
+                                                      nsteps):
+    """Aligned and with the state one element off: the bits of single steps,
+    and the oracle's values."""
+    import torch
+    from helpers import spec_for
+    from paper_1508_02899_amd import Lattice
+    f0, u, p = make_case(1, nx, nv, dtype=dtype, seed=nx + nv, nsub=nsub)
+    spec = spec_for(f0, p, dtype)
+    start, ud = torch.from_numpy(f0).cuda(), torch.from_numpy(u).cuda()
+    args = (p["tau_p"], p["kappa"], p["dt"])
+    with Lattice(spec) as lat:
+        ref = start.clone()
+        for _ in range(nsteps):
+            lat.step(ref, ud, *args, 1)
+        lat.sync()
+        for off in (0, 1):
+            buf = torch.full((start.numel() + off,), float("nan"),
+                             dtype=start.dtype, device="cuda")
+            f = buf[off:].view(start.shape)
+            f.copy_(start)
+            lat.step(f, ud, *args, nsteps)
+            lat.sync()
+            assert torch.equal(f, ref)
+    bound = FP32_REL_L2 if dtype == "f32" else FP64_REL_L2
+    err = rel_l2(ref.cpu().numpy(), run_oracle(f0, u, p, nsteps))
+    say(f"  rel L2 {err:.2e}")
+    assert err <= bound
