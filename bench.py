@@ -60,8 +60,9 @@ WORKLOADS = {
                                kappa=1e-4, vmax=3.0, coarse=True,
                                st_set=(0.5, 2.0, 5.0)),
 }
-# The sources of the step kernel of each dimension: counters recorded in
-# profiles/ count only while these hash to the recorded value.
+# The sources of the step kernel of each dimension, and of the kernels that
+# take several steps or sub-steps a launch: counters recorded in profiles/
+# count only while these hash to the recorded value.
 KERNEL_SOURCES = {
     2: ["paper_1508_02899_amd/csrc/step2d.h",
         "paper_1508_02899_amd/csrc/device_common.h"],
@@ -73,6 +74,19 @@ KERNEL_SOURCES = {
         "paper_1508_02899_amd/csrc/parts1d.h",
         "paper_1508_02899_amd/csrc/column1d.h",
         "paper_1508_02899_amd/csrc/device_common.h"],
+    "k_step1d_multi": ["paper_1508_02899_amd/csrc/step1d_multi.h",
+                       "paper_1508_02899_amd/csrc/step1d_multi.hip",
+                       "paper_1508_02899_amd/csrc/step1d_multi_f64.hip",
+                       "paper_1508_02899_amd/csrc/parts1d.h",
+                       "paper_1508_02899_amd/csrc/column1d.h",
+                       "paper_1508_02899_amd/csrc/device_common.h"],
+    "k_step2d_sub": ["paper_1508_02899_amd/csrc/step2d_sub.h",
+                     "paper_1508_02899_amd/csrc/step2d_sub_f32a.hip",
+                     "paper_1508_02899_amd/csrc/step2d_sub_f32b.hip",
+                     "paper_1508_02899_amd/csrc/step2d_sub_f32c.hip",
+                     "paper_1508_02899_amd/csrc/step2d_sub_f64.hip",
+                     "paper_1508_02899_amd/csrc/step2d.h",
+                     "paper_1508_02899_amd/csrc/device_common.h"],
 }
 
 
@@ -80,23 +94,74 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def kernel_hash(dim: int) -> str:
+def kernel_hash(key) -> str:
     h = hashlib.sha256()
-    for p in KERNEL_SOURCES[dim]:
+    for p in KERNEL_SOURCES[key]:
         with open(os.path.join(ROOT, p), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
 
-def step_kernel(dim, n, nv, dtype):
-    """The step kernel the library runs for this lattice (2D: k_step2d; 1D:
-    the split-column pass up to 2^19 sites for the velocity counts it is
-    built for, else one lane per site; short 1D lattices take several steps
-    per launch with the same update)."""
+def steps_per_launch(n, nv, dtype, nsub=1, shift=1):
+    """Time steps a launch of the 1D several-steps pass takes through LDS at
+    most (1: the lattice has no such pass, or is past its size)."""
+    weight = nsub * (2 if dtype == "f64" else 1)
+    most = (65536 if weight <= 1 else 32768 if weight <= 3 else
+            16384 if weight <= 8 else 8192 if weight <= 10 else 0)
+    if nv not in (3, 5, 7, 9, 13, 17, 21, 25, 33) or n > most:
+        return 1
+    halo = 128  # sites of a region beyond its finished ones (32 or 64)
+    return max(1, min(16, halo // (2 * shift * ((nv - 1) // 2))))
+
+
+def sub_steps_per_pass(n, nv, dtype, nsub, scheme="koren"):
+    """Collision sub-steps the next 2D pass takes of nsub, for the lattices
+    measured here: FP32 states past 128 MiB of 25^2 velocities or more share
+    a pass, the smaller 256^2 x 17^2 does not."""
+    if dtype != "f32" or nv < 25 or nv * nv * n * n * 4 <= (128 << 20):
+        return 1
+    if nsub >= 4 and (nv >= 65 or scheme == "upwind"):
+        return 4
+    return min(nsub, 2)
+
+
+def step_kernel(dim, n, nv, dtype, steps=1, nsub=1, shift=1, scheme="koren"):
+    """The step kernel the library runs for a call of `steps` steps on this
+    lattice (2D: k_step2d, or k_step2d_sub where sub-steps share a pass; 1D:
+    several steps per launch for short lattices, else the split-column pass
+    up to 2^19 sites for the velocity counts it is built for, else one lane
+    per site)."""
     if dim == 2:
-        return "k_step2d"
+        return ("k_step2d_sub"
+                if sub_steps_per_pass(n, nv, dtype, nsub, scheme) > 1
+                else "k_step2d")
+    if steps > 1 and steps_per_launch(n, nv, dtype, nsub, shift) > 1:
+        return "k_step1d_multi"
     parts = nv in (17, 33, 65) or (nv == 129 and dtype == "f32")
     return "k_step1d_parts" if parts and n <= (1 << 19) else "k_step1d"
+
+
+def step_launches(dim, n, nv, dtype, steps, nsub=1, shift=1, scheme="koren"):
+    """Launches of that kernel in such a call (2D: without the further half
+    pass that an odd number of them may start with; 1D: with the further
+    launch that makes their number even where the state is too large to be
+    copied cheaply)."""
+    if dim == 2:
+        passes, left = 0, nsub
+        while left > 0:
+            left -= sub_steps_per_pass(n, nv, dtype, left, scheme)
+            passes += 1
+        return passes * steps
+    per = steps_per_launch(n, nv, dtype, nsub, shift)
+    if steps < 2 or per < 2:
+        return steps
+    launches = -(-steps // per)
+    cheap = n * nv * (8 if dtype == "f64" else 4) <= 5 << 19
+    return launches if cheap else launches + launches % 2
+
+
+def traffic_key(dim, kernel):
+    return kernel if kernel in KERNEL_SOURCES else dim
 
 
 def geometry(w):
@@ -659,12 +724,17 @@ def summarize(args):
     if w.get("batch") and not w.get("st_set"):
         return summarize_batch(args)
     trace, fetch, write = (_rocpd(d) for d in args.summarize)
-    kern = step_kernel(w["dim"], w["n"], w["nv"], w["dtype"])
+    kern = step_kernel(w["dim"], w["n"], w["nv"], w["dtype"], args.steps,
+                       shift=w["s"])
     elem = 8 if w["dtype"] == "f64" else 4
     ny = w["n"] if w["dim"] == 2 else 1
     sites = w["n"] * ny
     cells = sites * w["nv"] ** w["dim"]
-    algo = 2 * cells * elem + w["dim"] * sites * elem
+    steps = (args.steps if kern == "k_step1d_multi" else 1)
+    if steps > 1:  # of a launch: they are spread evenly over the launches
+        steps /= step_launches(1, w["n"], w["nv"], w["dtype"], steps,
+                               shift=w["s"])
+    algo = round(2 * cells * elem + w["dim"] * sites * elem * steps)
     # the copy kernel moves the whole span of the state (its padding too)
     from paper_1508_02899_amd import LatticeSpec
     from paper_1508_02899_amd.lattice import recommended_pitch
@@ -693,7 +763,7 @@ def summarize(args):
     fw = state / 1024.0 / w_c
     traffic = (f_k * ff + w_k * fw) * 1024.0
     out = {"workload": args.workload, "kernel": kern,
-           "kernel_hash": kernel_hash(w["dim"]),
+           "kernel_hash": kernel_hash(traffic_key(w["dim"], kern)),
            "bytes_per_launch": round(traffic),
            "read_bytes": round(f_k * ff * 1024.0),
            "write_bytes": round(w_k * fw * 1024.0),
@@ -868,7 +938,7 @@ def main():
         lat.sync()
     # Launch durations over the timed region itself: one event pair on the
     # library's stream (torch's current one) around the K steps, recorded
-    # before the final moments (the span holds the K step launches and the
+    # before the final moments (the span holds the step launches and the
     # device CFL check of their flow slices, about 0.2 % of it).  Events
     # around every launch would cost time themselves (on the 2D workload
     # 464 us per launch against 457 us back to back).  A second pass of the
@@ -898,9 +968,10 @@ def main():
     ev3.record()
     torch.cuda.synchronize()
     lat.sync()
-    # a step reads and writes the state at least once; the library may make
-    # several passes of its sub-steps, or one launch of several short steps
-    kern2_ms, launches = ev2.elapsed_time(ev3), K
+    kern2_ms = ev2.elapsed_time(ev3)
+    kern = step_kernel(dim, n, nv, w["dtype"], K, nsub, w["s"], args.scheme)
+    launches = step_launches(dim, n, nv, w["dtype"], K, nsub, w["s"],
+                             args.scheme)
     if args.copy_calibration:
         g = spec.empty_state()
         lat.copy_state(g, f)
@@ -921,10 +992,12 @@ def main():
     sec = ev_ms / 1e3
     value = cells * K / sec / 1e9
     avg_launch_s = kern_ms / 1e3 / max(launches, 1)
-    algo_bytes = 2 * cells * elem + dim * sites * elem  # read f, write f, u
+    # a launch reads f and writes f once, and the flow of each of its steps
+    algo_bytes = 2 * cells * elem + round(
+        dim * sites * elem * max(1.0, K / max(launches, 1)))
     achieved = algo_bytes / avg_launch_s / 1e9
     mass_drift = abs(m1["mass"] - m0["mass"]) / m0["mass"]
-    traffic = load_traffic(args.workload)
+    traffic = load_traffic(args.workload, traffic_key(dim, kern))
     out = {
         "metric": METRIC,
         "value": round(value, 3),
@@ -965,7 +1038,8 @@ def main():
             "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
-            "kernel": step_kernel(dim, n, nv, w["dtype"]),
+            "kernel": kern,
+            "launches": launches,
             "avg_launch_us": round(avg_launch_s * 1e6, 3),
             "launch_timing": ("one HIP event pair around the K steps of the "
                               "timed region (before its final moments; the "
