@@ -81,6 +81,7 @@ KERNEL_SOURCES = {
                        "paper_1508_02899_amd/csrc/column1d.h",
                        "paper_1508_02899_amd/csrc/device_common.h"],
     "k_step2d_sub": ["paper_1508_02899_amd/csrc/step2d_sub.h",
+                     "paper_1508_02899_amd/csrc/step2d_sub.hip",
                      "paper_1508_02899_amd/csrc/step2d_sub_f32a.hip",
                      "paper_1508_02899_amd/csrc/step2d_sub_f32b.hip",
                      "paper_1508_02899_amd/csrc/step2d_sub_f32c.hip",

@@ -240,7 +240,8 @@ int lattice_density(lattice_t* L, const void* f, double dt, double* rho);
  * <rho_r> = 1).  out: host, levels doubles.  nx (and ny in 2D) must be
  * multiples of 2^(levels-1); levels <= 32.  FP64 sums in a fixed order
  * (bit-reproducible).  Synchronous; the first call allocates a small device
- * workspace that the handle keeps.  EINVAL, ENOMEM, ENONFINITE (zero or non-finite mass), EHIP.
+ * workspace that the handle keeps.  EINVAL, ENOMEM, ENONFINITE (zero or
+ * non-finite mass), EHIP.
  */
 int lattice_rho_r2(lattice_t* L, const double* rho, int levels, double* out);
 
@@ -292,9 +293,10 @@ int lattice_s1(lattice_t* L, const void* f, double dt, int32_t nr,
  *   spacing dx of the lattice (domain nx dx by ny dx).  Two separable passes
  *   (along x, then along y) through a workspace of 4 (kmax + 1) nx reals
  *   per slice, of which the handle keeps up to 32 MB (or one slice's) from
- *   the first call on; more slices go through it in turn.  A call under
- *   stream capture uses a stream-ordered temporary instead.  1 <= kmax <= 64,
- *   2 kmax < nx, ny; n_slices, ny <= 65535.  EINVAL, EHIP.
+ *   the first call on, allocated in the order of its stream; more slices go
+ *   through it in turn.  A call under stream capture uses a stream-ordered
+ *   temporary instead.  1 <= kmax <= 64, 2 kmax < nx, ny; n_slices, ny <=
+ *   65535.  EINVAL, EHIP.
  */
 int lattice_flow1d_modes(lattice_t* L, int32_t nmodes, const float* coef,
                          int64_t n_slices, void* u);
@@ -320,9 +322,10 @@ int lattice_sync(lattice_t* L);
 
 /* Per-launch timing of the streaming/collision kernels with HIP events on
  * the handle's stream.  While it is on, every step of a short 1D lattice is
- * a launch of its own (otherwise one launch takes several steps).  enable != 0 starts recording (and resets the
- * totals); lattice_profile_read waits for the stream and returns the summed
- * kernel time in milliseconds and the number of timed launches. */
+ * a launch of its own (otherwise one launch takes several steps), with the
+ * same results.  enable != 0 starts recording (and resets the totals);
+ * lattice_profile_read waits for the stream and returns the summed kernel
+ * time in milliseconds and the number of timed launches. */
 int lattice_profile(lattice_t* L, int enable);
 int lattice_profile_read(lattice_t* L, double* total_ms, int64_t* launches);
 

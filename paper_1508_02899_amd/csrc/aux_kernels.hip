@@ -252,8 +252,8 @@ void density_go(const T* f, int64_t sites, int64_t pitch, int nplanes,
 // Flow check: flag |= 1 if some |u| exceeds umax_ok (>= when strict) or is
 // not finite.  Grid-stride, one atomic per offending wavefront.
 // With n16 > 0 also the copy of n16 16-byte pieces and tail more bytes that a
-// call of an odd number of passes starts with: one launch instead of two, which is what a
-// call of a single step on a small lattice consists of.
+// call of an odd number of passes starts with: one launch instead of two,
+// which is what a call of a single step on a small lattice consists of.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_cfl_check(
     const T* __restrict__ u, int64_t n, T umax_ok, int strict,

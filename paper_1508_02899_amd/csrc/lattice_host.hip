@@ -305,10 +305,10 @@ static int run_call(const lattice_desc& d, CallPlan& p, void* f,
   // launches; profiled runs time every step by itself.  An odd number of
   // launches starts from a copy, which the flow check's launch makes where
   // both buffers are 16-byte aligned: cheaper than one more launch while the
-  // state is small (a call of 2 and 5 steps,
-  // us, a further launch against the copy: 0.5 MB, 8192 x 17, 12.2, 12.5 ->
-  // 9.0, 8.9; 2.1 MB, 8192 x 33 FP64, 11.5, 14.4 -> 9.1, 14.2; 4.3 MB, 32768 x
-  // 17 FP64, 11.6, 21.6 -> 14.2, 20.6).
+  // state is small (a call of 2 and 5 steps, us, a further launch against the
+  // copy: 0.5 MB, 8192 x 17, 12.2, 12.5 -> 9.0, 8.9; 2.1 MB, 8192 x 33 FP64,
+  // 11.5, 14.4 -> 9.1, 14.2; 4.3 MB, 32768 x 17 FP64, 11.6, 21.6 -> 14.2,
+  // 20.6).
   constexpr int64_t kCheapCopy = 5 << 19;
   int64_t launches = p.passes;
   if (d.dim == 1 && stream && nsteps > 1 && !(L && L->prof)) {

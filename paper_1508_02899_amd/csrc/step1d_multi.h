@@ -1,22 +1,23 @@
 // step1d_multi.h -- several 1D time steps per launch for short lattices
 // (gfx950).
 //
-// A short lattice (up to a few thousand sites) leaves the chip idle and its
-// step is a launch: the host issues one every 2.9 us (8 us for the first
-// fifty after an idle queue), whatever the step computes.  Here a workgroup
-// takes G sites through T steps in LDS.  The mass of velocity index j moves
-// s (j - h) cells per step, so G finished sites need the start values of the
-// sites up to h s T away on either side: the workgroup loads G + 2 h s T
-// sites and updates a region that shrinks by h s on either side per step.
+// A short lattice (up to 8192 sites, and with few sub-steps up to 65536:
+// step1d_multi_lattice) leaves the chip idle and its step is a launch: the
+// host issues one every 2.9 us (8 us for the first fifty after an idle
+// queue), whatever the step computes.  Here a workgroup takes G sites through
+// T steps in LDS.  The mass of velocity index j moves s (j - h) cells per
+// step, so G finished sites need the start values of the sites up to h s T
+// away on either side: the workgroup loads G + 2 h s T sites and updates a
+// region that shrinks by h s on either side per step.
 // The neighbours compute the same halo sites again from the same values with
 // the same operations; no workgroup waits for another.  The update is the
 // split-column one (parts1d.h), bit for bit that of the one-step pass of the
 // same lattice (step1d_parts.hip, or step1d.hip with the same arithmetic).
-// Measured per step of a long call (one launch per step
-// before): 256 x 33 FP64 4.35 -> 2.24 us, 256 x 17 FP32 3.1 -> 1.0, 4096 x 9
-// FP32 3.85 -> 0.74, 16384 x 33 FP32 3.6 -> 1.7.  What is left is the update
-// of the region by one compute unit and, per launch, one load and one store
-// latency.
+// Measured per step of a call of 200 (one launch per step before): 256 x 33
+// FP64 3.7 -> 2.1 us, 256 x 17 FP32 2.8 -> 1.0, 4096 x 9 FP32 3.75 -> 0.75,
+// 16384 x 33 FP32 3.4 -> 1.7, 65536 x 17 FP32 4.0 -> 2.7.  What is left is the
+// update of the region by one compute unit and, per launch, one load and one
+// store latency.
 #pragma once
 
 #include "lattice_internal.h"
@@ -24,10 +25,10 @@
 
 namespace lat {
 
-// Finished sites G, sites loaded at most.  32
-// sites spread a short lattice over the most compute units; from 257 such
-// workgroups on, 64 sites recompute less (16384 x 33 FP64: 4.3 us a step with
-// 32, 2.7 with 64; 256 x 33 FP64: 2.2 with 32, 2.4 with 64).
+// Finished sites G, sites loaded at most.  32 sites spread a short lattice
+// over the most compute units; from 257 such workgroups on, 64 sites
+// recompute less (16384 x 33 FP64: 4.3 us a step with 32, 2.7 with 64; 256 x
+// 33 FP64: 2.2 with 32, 2.4 with 64).
 template <int G>
 struct MultiTile;
 template <> struct MultiTile<32> {
@@ -38,7 +39,10 @@ template <> struct MultiTile<64> {
 };
 
 // Velocity lattices with a kernel and the parts of their columns (lanes of
-// 3 to 6 cells; halving or doubling them changes the step by under 10 %).
+// 3 to 6 cells; halving or doubling them changes the step by under 10 %).  11,
+// 15, 19, 23, 27, 29 and 31 have none built and keep a launch per step; the
+// pass was not measured there.  From 65 velocities on a region of 160 sites
+// holds two steps at most, with two halo sites for each finished one and more.
 constexpr int multi_parts(int nv) {
   switch (nv) {
     case 3: return 1;
@@ -155,12 +159,12 @@ __global__ __launch_bounds__(64 * multi_waves<G>(NV)) void k_step1d_multi(
 
 template <typename T, int NV, int G>
 hipError_t launch_multi_g(const StepArgs& a, int nsteps, int64_t step0,
-                     int64_t u_hold, hipStream_t s) {
+                          int64_t u_hold, hipStream_t s) {
   const int nblocks = (int)((a.nx + G - 1) / G);
   const T as = (T)a.alpha_scale, be = (T)a.beta, D = (T)a.D;
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * multi_waves<G>(NV)), 0, s,
-                       (const T*)a.fin, (T*)a.fout, (const T*)a.u, a.flag,
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * multi_waves<G>(NV)),
+                       0, s, (const T*)a.fin, (T*)a.fout, (const T*)a.u, a.flag,
                        (int)a.nx, a.shift, a.nsub_inline, as, be, D, nsteps,
                        step0, u_hold, nblocks);
   };

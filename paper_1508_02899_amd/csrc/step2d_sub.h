@@ -13,6 +13,9 @@
 // passes of NV + 3.  Every element is read once and written once per pass,
 // and the bits are those of the separate passes.
 //
+// The Koren passes in two-wavefront stages fill the 256 registers and spill
+// four of them at 65 velocities (20 bytes a lane) and three at 33 (16 bytes).
+//
 // Bound by the arithmetic of the Koren fluxes (upwind: by memory) where the
 // lattice is large, by the latency of a tick where it is small.  256^2 sites
 // x 65^2, 4 sub-steps: 1646 -> 1359 us a step (four passes at 4.4 TB/s had
