@@ -1335,25 +1335,35 @@ hipError_t launch_mlp_correct(const CoarseGeom& g, const float* params,
   };
   // A wavefront corrects its sites one after the other, so the tile is as
   // small as still leaves the weights' loading a small share: the smaller the
-  // lattice, the more of the chip it then uses (two steps, us, threshold
-  // 8e-3, tiles of 32, 16, 8, 4 sites: 53 x 137 sites 318, 234, 210, 199;
-  // 128^2 398, 379, 347, 343; 180^2 638, 598, 592, 591; 240^2 1017, 938, 911,
-  // 940; 256^2 1057, 1020, 1047, 1059; 384^2 2166, 2168, 2208, 2291; 512^2
-  // 3774, 3819, 3858, 4094).  A cell lies in the stencils of ten faces at
-  // most, so a threshold of 0.1 leaves a site at most 100 of its 544 faces and
-  // 0.3 a third of that: then the weights are the larger share (two steps of
-  // 160^2, tiles of 32 and 4: threshold 0.05 351, 284 us; 0.1 218, 244; 0.3 146,
-  // 215; 53 x 37 sites, which leave compute units idle, 0.1 108, 58).
-  if (g.line_eps >= 0.1f && S > 8000)
-    go(k_mlp_correct17<32>, 32);
-  else if (S <= 28000)
-    go(k_mlp_correct17<4>, 4);
-  else if (S <= 60000)
-    go(k_mlp_correct17<8>, 8);
-  else if (S <= 120000)
-    go(k_mlp_correct17<16>, 16);
+  // lattice, the more of the chip it then uses, and the fewer faces pass, the
+  // larger that share.  Measured on states of a learned coarse run at St 5 (ten
+  // steps in a call, us a step, tiles of 4, 8, 16, 32 sites; before the tiles
+  // depended on the size all took 32):
+  //   threshold 8e-3: 6000 sites 49, 48, 55, 73; 12800 76, 76, 84, 86; 16384
+  //     91, 83, 86, 87; 40000 169, 156, 157, 161; 59536 247, 226, 219, 230;
+  //     65536 277, 254, 239, 237; 160000 774, 608, 574, 570
+  //   0.048: 2500 33, 36, 43, 61; 6000 47, 44, 50, 65; 12800 72, 68, 75, 76;
+  //     16384 86, 75, 78, 76; 25600 111, 98, 102, 114; 40000 154, 136, 134, 141;
+  //     59536 225, 193, 186, 192; 65536 250, 220, 204, 201
+  //   0.3: 9000 56, 49, 48, 58; 12800 71, 61, 59, 55; 40000 160, 109, 103, 98
+  // and where a state spread over the velocity square leaves no face at 0.048:
+  //   16384 sites 74, 58, 48, 40; 25600 102, 73, 61, 55; 40000 143, 93, 79, 68;
+  //   65536 234, 157, 111, 95.
+  // A cell lies in the stencils of ten faces at most, so a threshold of 0.1
+  // leaves a site at most 100 of its 544 faces and 0.3 a third of that.
+  int ts;
+  if (g.line_eps >= 0.1f)
+    ts = S <= 3000 ? 4 : S <= 12000 ? 8 : 32;
+  else if (g.line_eps >= 0.02f)
+    ts = S <= 3000 ? 4 : S <= 15000 ? 8 : S <= 62000 ? 16 : 32;
   else
-    go(k_mlp_correct17<32>, 32);
+    ts = S <= 14000 ? 4 : S <= 62000 ? 8 : S <= 120000 ? 16 : 32;
+  switch (ts) {
+    case 4: go(k_mlp_correct17<4>, 4); break;
+    case 8: go(k_mlp_correct17<8>, 8); break;
+    case 16: go(k_mlp_correct17<16>, 16); break;
+    default: go(k_mlp_correct17<32>, 32);
+  }
   return hipGetLastError();
 }
 

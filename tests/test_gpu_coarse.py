@@ -473,3 +473,13 @@ def test_correction_at_thresholds_that_leave_few_faces(eps, rep):
     say(f"  {kept} of {nx * ny} sites without faces")
     assert 0 < kept < nx * ny
     m.close()
+
+
+@pytest.mark.parametrize("eps,rep", [
+    (0.0199, 29), (0.0199, 30), (0.02, 13), (0.02, 14), (0.048, 30),
+    (0.064, 31), (0.064, 62), (0.064, 63), (0.1, 27), (0.1, 28)])
+def test_correction_tiles_by_threshold(eps, rep):
+    """The same on both sides of the other lines of the tile rule: the
+    threshold 0.02, and the sizes at which a lattice takes tiles of 8, 16 and
+    32 sites (16 rep^2 sites)."""
+    test_correction_at_thresholds_that_leave_few_faces(eps, rep)
